@@ -134,11 +134,26 @@ __device__ __forceinline__ void dft_l(cpx<T>* v) {
 // whether consecutive threads walk rows (column layouts) or the L threads of
 // one row.  Every thread of the block must call it (it synchronises).
 // ---------------------------------------------------------------------------
-// The first read phase takes its inputs from load(r, e) and the last write
-// phase hands its outputs to store(r, e, value), so a caller can fuse a
-// conversion or rearrangement into the transform's own passes; the exchange
-// in between goes through buf.  Every read made by load happens before the
-// first barrier, so buf may alias what load reads.
+// The first read phase takes its inputs from load(v, r, elem), which fills
+// v[i] with element elem(i) of row r for i < 16 (all 16 at once, so that a
+// loader that adds several partial inputs keeps 16 loads in flight per
+// partial), and the last write phase hands its outputs to store(r, e, value),
+// so a caller can fuse a conversion or rearrangement into the transform's own
+// passes; the exchange in between goes through buf.  Every read made by load
+// happens before the first barrier, so buf may alias what load reads.
+// Batched loader of a per-element one.
+template <typename F>
+struct EachElem {
+  F f;
+  template <typename C, typename E>
+  __device__ __forceinline__ void operator()(C (&v)[16], int r, E elem) const {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = f(r, elem(i));
+  }
+};
+template <typename F>
+__device__ __forceinline__ EachElem<F> each_elem(F f) { return {f}; }
+
 template <typename T, int L, bool INV, bool PAD, typename LoadF, typename StoreF>
 __device__ __forceinline__ void fft_rows_reg_io(cpx<T>* buf, int nrows, int rstride, int estride, bool rows_fast,
                                                 const cpx<T>* tw, int twN, LoadF load, StoreF store) {
@@ -155,10 +170,7 @@ __device__ __forceinline__ void fft_rows_reg_io(cpx<T>* buf, int nrows, int rstr
   const int step = twN / N;
   cpx<T> v[16];
   if constexpr (!INV) {
-    if (act) {
-#pragma unroll
-      for (int n1 = 0; n1 < 16; ++n1) v[n1] = load(r, l + L * n1);
-    }
+    if (act) load(v, r, [=](int n1) { return l + L * n1; });
     __syncthreads();
     if (act) {
       dft16<T, false>(v);
@@ -183,13 +195,7 @@ __device__ __forceinline__ void fft_rows_reg_io(cpx<T>* buf, int nrows, int rstr
     }
     __syncthreads();
   } else {
-    if (act) {
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-#pragma unroll
-        for (int k2 = 0; k2 < L; ++k2) v[j * L + k2] = load(r, l * J + j + 16 * k2);
-      }
-    }
+    if (act) load(v, r, [=](int i) { return l * J + i / L + 16 * (i % L); });  // v[j L + k2]
     __syncthreads();
     if (act) {
 #pragma unroll
@@ -226,7 +232,7 @@ __device__ __forceinline__ void fft_rows_reg(cpx<T>* buf, int nrows, int rstride
                                              const cpx<T>* tw, int twN) {
   auto elem = [=](int r, int e) -> cpx<T>& { return buf[r * rstride + (PAD ? lds_pad(e) : e * estride)]; };
   fft_rows_reg_io<T, L, INV, PAD>(
-      buf, nrows, rstride, estride, rows_fast, tw, twN, [&](int r, int e) { return elem(r, e); },
+      buf, nrows, rstride, estride, rows_fast, tw, twN, each_elem([&](int r, int e) { return elem(r, e); }),
       [&](int r, int e, const cpx<T>& x) { elem(r, e) = x; });
 }
 
