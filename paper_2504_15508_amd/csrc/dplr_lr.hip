@@ -62,12 +62,6 @@ static_assert(DPLR_SORT_CHUNKS >= 1 && DPLR_SORT_CHUNKS <= 256, "sort chunk coun
 #ifndef DPLR_IFFTX_ROWS
 #define DPLR_IFFTX_ROWS 16
 #endif
-#ifndef DPLR_IXY_MIN_THREADS
-#define DPLR_IXY_MIN_THREADS 64
-#endif
-#ifndef DPLR_IXY_AD_THREADS
-#define DPLR_IXY_AD_THREADS 64
-#endif
 #ifndef DPLR_MIXED_QSHIFT
 #define DPLR_MIXED_QSHIFT 4
 #endif
@@ -106,8 +100,8 @@ bool tuned_mesh(const int* K) {
   return true;
 }
 
-int round_threads(long elems) {
-  long t = (elems + kEPT - 1) / kEPT;
+int round_threads(long elems, int ept) {
+  long t = (elems + ept - 1) / ept;
   t = ((t + 63) / 64) * 64;
   if (t < 64) t = 64;
   if (t > 1024) t = 1024;
@@ -167,6 +161,7 @@ struct dplr_lr_plan_s {
   size_t lds_spread = 0, lds_ffty = 0, lds_z = 0, lds_ifftx = 0, lds_ixy = 0;
   bool plane = false;         // whole z planes fit in LDS: spread + x and y transforms in one kernel
   bool ixy = false;           // inverse y and x transforms of a plane component in one kernel
+  int nzout = 3;              // spectra out of the z pass: three components, A and B, or the potential
   bool mixed = false;         // mesh outside the tuned kernels: mixed-radix path
   long long* mmesh = nullptr; // mixed-radix path: fixed-point mesh [Kz][Ky][Kx]
   void* mspec = nullptr;      // ... its full complex spectrum
@@ -281,6 +276,7 @@ bool choose_geometry(dplr_lr_plan p) {
   g.twN = std::max(Kx, std::max(Ky, Kz));
   const size_t twb = g.twN * cs;
   const size_t budget = p->lds_budget - 1024;  // static LDS (ranges, reductions)
+  const int ept = p->fp64 ? fft_ept<double>() : fft_ept<float>();
 
   // plane spread: one z plane of 64-bit accumulators (rows of Kx + p - 1),
   // reused for the x- and y-transform tiles, 1024 threads holding at most 16
@@ -335,7 +331,7 @@ bool choose_geometry(dplr_lr_plan p) {
     if (!g.scy) return false;
     g.spy = Ky / g.scy; g.spz = Kz / g.scz;
     // the in-place fixed-point conversion holds at most 16 values per thread
-    p->thr_spread = std::max(DPLR_SPREAD_MIN_THREADS, round_threads((long)g.scy * g.scz / 2 * Kx));
+    p->thr_spread = std::max(DPLR_SPREAD_MIN_THREADS, round_threads((long)g.scy * g.scz / 2 * Kx, ept));
     while ((long)p->thr_spread * 16 < (long)g.scy * g.scz * Kx && p->thr_spread < 512) p->thr_spread += 64;
     if ((long)p->thr_spread * 16 < (long)g.scy * g.scz * Kx || p->thr_spread > 512) return false;
     // x splits: more blocks when the pencils alone do not fill the device
@@ -350,38 +346,36 @@ bool choose_geometry(dplr_lr_plan p) {
   // inverse x pass: xyb rows of y of the three fields per block
   g.xyb = std::min(DPLR_IFFTX_ROWS, Ky);
   while (g.xyb > 2 && ((size_t)(3 * g.xyb / 2) * (padded_len(Kx) + 1) * cs + twb > budget ||
-                       (long)(3 * g.xyb / 2) * Kx > (long)kEPT * 512))
+                       (long)(3 * g.xyb / 2) * Kx > (long)ept * 512))
     g.xyb /= 2;
   p->lds_ifftx = (size_t)(3 * g.xyb / 2) * (padded_len(Kx) + 1) * cs + twb;
-  p->thr_ifftx = std::max(round_threads((long)(3 * g.xyb / 2) * Kx), ((3 * g.xyb / 2 + 63) / 64) * 64);
+  p->thr_ifftx = std::max(round_threads((long)(3 * g.xyb / 2) * Kx, ept), ((3 * g.xyb / 2 + 63) / 64) * 64);
   if (p->thr_ifftx > 512) return false;
 
   // y pass: blocks of zb contiguous rows, about 1024 complex elements
   g.zb = std::max(1, std::min(Kz, DPLR_FFTY_ELEMS / Ky));
   while (g.zb > 1 && ((size_t)g.zb * (padded_len(Ky) + 1) * cs + twb > budget ||
-                      round_threads((long)g.zb * Ky) > kFftyThreads))
+                      round_threads((long)g.zb * Ky, ept) > kFftyThreads))
     g.zb /= 2;
-  p->thr_ffty = round_threads((long)g.zb * Ky);
+  p->thr_ffty = round_threads((long)g.zb * Ky, ept);
   if (p->thr_ffty > kFftyThreads) return false;
   // the inverse pass also hosts the final reduction: 7 doubles per thread
   p->lds_ffty = std::max((size_t)g.zb * (padded_len(Ky) + 1) * cs + twb, (size_t)7 * p->thr_ffty * sizeof(double));
 
-  // z pass: yb columns x Kz x 3 fields
+  // z pass: yb columns x Kz x nzout spectra.  FP32 plane meshes keep three field
+  // spectra, the others A and B (k_fftz_poisson); the potential needs one, in
+  // the layout of two
   g.yb = std::min(DPLR_FFTZ_COLS, Ky);
-  while (g.yb > 1 && ((size_t)3 * g.yb * Kz * cs + twb > budget || (long)3 * g.yb * Kz > (long)kEPT * 1024)) g.yb /= 2;
-  p->lds_z = (size_t)3 * g.yb * Kz * cs + twb;
-  p->thr_z = round_threads((long)3 * g.yb * Kz);
+  while (g.yb > 1 && ((size_t)3 * g.yb * Kz * cs + twb > budget || (long)3 * g.yb * Kz > (long)16 * 1024)) g.yb /= 2;
   g.nzblk = g.Kh * (Ky / g.yb);
   g.zgroup = std::max<int>(1, (int)(128 / (g.yb * cs)));
 
   // fused inverse y + x pass (plane mode): one block per (z plane, component)
   p->ixy = false;
   if (p->plane && Kz % 8 == 0) {
-    const long e_y = (long)g.Kh * Ky, e_x = (long)(Ky / 2) * Kx;
-    // analytic differentiation has one component per plane (Kz blocks): more threads per block
-    const int thr_min = (p->cfg.flags & DPLR_LR_DIFF_AD) ? DPLR_IXY_AD_THREADS : DPLR_IXY_MIN_THREADS;
-    const int thr = std::max(thr_min, (int)(((std::max(e_y, e_x) + kEPT - 1) / kEPT + 63) / 64 * 64));
-    const size_t b_y = (size_t)g.Kh * (padded_len(Ky) + 1) * cs, b_x = (size_t)(Ky / 2) * (padded_len(Kx) + 1) * cs;
+    const int rows = p->fp64 ? Kx / 2 : g.Kh;  // FP64 packs the kx = 0 and Kx/2 rows
+    const int thr = (int)(((long)rows * Ky + ept - 1) / ept + 63) / 64 * 64;
+    const size_t b_y = (size_t)rows * (padded_len(Ky) + 1) * cs, b_x = (size_t)(Ky / 2) * (padded_len(Kx) + 1) * cs;
     const size_t lds = std::max(std::max(b_y, b_x) + twb, (size_t)7 * thr * sizeof(double));
     if (thr <= 1024 && lds <= budget) {
       p->ixy = true;
@@ -389,6 +383,12 @@ bool choose_geometry(dplr_lr_plan p) {
       p->lds_ixy = lds;
     }
   }
+  p->nzout = (p->ixy && !p->fp64) ? 3 : 2;
+  const int zcols = p->nzout * g.yb;
+  // the potential runs in the ik plan's launch shape, whose FP64 sums it repeats
+  if (p->cfg.flags & DPLR_LR_DIFF_AD) p->nzout = 1;
+  p->lds_z = (size_t)zcols * Kz * cs + twb;
+  p->thr_z = round_threads((long)zcols * Kz, ept);
   return true;
 }
 
@@ -546,8 +546,8 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
     }
     {
       ProfScope ps(p, 4);
-      hipLaunchKernelGGL((k_ffty<T, false>), dim3(g.Kh * (g.K[2] / g.zb)), dim3(p->thr_ffty), p->lds_ffty, s, spec, tw,
-                         g, g.nsplit, nspec, (const double*)nullptr, 0.0, (double*)nullptr, (double*)nullptr);
+      hipLaunchKernelGGL((k_ffty<T, false>), dim3(g.Kh * (g.K[2] / g.zb)), dim3(p->thr_ffty), p->lds_ffty, s, spec, 1,
+                         tw, g, g.nsplit, nspec, (const double*)nullptr, 0.0, (double*)nullptr, (double*)nullptr);
     }
   }
   PoissonConsts pc;
@@ -556,35 +556,36 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
   // field components: three (ik) or the potential alone (analytic differentiation)
   const bool ad = (p->cfg.flags & DPLR_LR_DIFF_AD) != 0;
   const int ncomp = ad ? 1 : 3;
+  const int xpad = ad ? kGatherAdPad : P - 1;  // repeated records per field row
   {
     ProfScope ps(p, 5);
     hipLaunchKernelGGL((k_fftz_poisson<T>), dim3((g.nzblk + 8 * g.zgroup - 1) / (8 * g.zgroup) * 8 * g.zgroup),
                        dim3(p->thr_z), p->lds_z, s, spec,
-                       p->plane ? g.nsplit : 1, nspec, ncomp, fspec, p->G, p->partials, tw, g, pc);
+                       p->plane ? g.nsplit : 1, nspec, p->nzout, p->ixy ? 1 : 2, fspec, p->G, p->partials, tw, g, pc);
   }
   const double V = p->box[0] * p->box[1] * p->box[2];
   const bool want_virial = !(p->cfg.flags & DPLR_LR_NO_VIRIAL) && virial;
   if (p->ixy) {
     ProfScope ps(p, 10);
     hipLaunchKernelGGL((k_ifft_xy<T>), dim3(ncomp * g.K[2]), dim3(p->thr_ixy), p->lds_ixy, s, fspec,
-                       reinterpret_cast<T*>(p->field), ncomp, ad ? kGatherAdPad : 0, tw, g, (const double*)p->partials,
+                       reinterpret_cast<T*>(p->field), ncomp, xpad, tw, g, (const double*)p->partials,
                        p->cfg.coulomb_k / (2.0 * V), energy, want_virial ? virial : (double*)nullptr);
   } else {
     ProfScope ps(p, 6);
-    hipLaunchKernelGGL((k_ffty<T, true>), dim3(ncomp * g.Kh * (g.K[2] / g.zb)), dim3(p->thr_ffty), p->lds_ffty, s,
-                       fspec, tw, g, 1, (size_t)0, (const double*)p->partials, p->cfg.coulomb_k / (2.0 * V), energy,
+    hipLaunchKernelGGL((k_ffty<T, true>), dim3((ad ? 1 : 2) * g.Kh * (g.K[2] / g.zb)), dim3(p->thr_ffty), p->lds_ffty,
+                       s, fspec, ncomp, tw, g, 1, (size_t)0, (const double*)p->partials, p->cfg.coulomb_k / (2.0 * V), energy,
                        want_virial ? virial : (double*)nullptr);
   }
   if (n > 0) {
     if (!p->ixy) {
       ProfScope ps(p, 7);
       hipLaunchKernelGGL((k_ifftx<T>), dim3(g.K[2] * (g.K[1] / g.xyb)), dim3(p->thr_ifftx), p->lds_ifftx, s, fspec,
-                         reinterpret_cast<T*>(p->field), ncomp, tw, g);
+                         reinterpret_cast<T*>(p->field), ncomp, xpad, tw, g);
     }
     {
       ProfScope ps(p, 8);
       constexpr int kXcd = 8;  // MI355X: 8 XCDs, blocks dealt round-robin
-      const int per_block = 4 * (64 / P);
+      const int per_block = ad ? 4 * (64 / P) : GatherSplit<T, P>::kPerBlock;
       const int nchunks = (int)((n + per_block - 1) / per_block);
       const int nblk = (nchunks + kXcd - 1) / kXcd * kXcd;
       const int acc = (p->cfg.flags & DPLR_LR_ACCUMULATE) ? 1 : 0;
@@ -602,9 +603,13 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
                            (T*)ion_force, (T*)wc_force, n_ion, (T)(p->cfg.coulomb_k / V), (T)(g.K[0] / p->box[0]),
                            (T)(g.K[1] / p->box[1]), (T)(g.K[2] / p->box[2]), acc, kXcd, g);
       } else {
-        hipLaunchKernelGGL((k_gather<T, P>), dim3(nblk), dim3(256), 0, s, reinterpret_cast<const F3<T>*>(p->field),
+        // A and B carry integer wave indices
+        double fs[3] = {p->cfg.coulomb_k / V, p->cfg.coulomb_k / V, p->cfg.coulomb_k / V};
+        if (p->nzout == 2)
+          for (int a = 0; a < 3; ++a) fs[a] *= pc.two_pi_over_L[a];
+        hipLaunchKernelGGL((k_gather<T, P>), dim3(nblk), dim3(256), 0, s, reinterpret_cast<const T*>(p->field),
                            sorted, p->sidx, p->perm, (int)n, nchunks, (T*)ion_force, (T*)wc_force, n_ion,
-                           (T)(p->cfg.coulomb_k / V), acc, kXcd, g);
+                           (T)fs[0], (T)fs[1], (T)fs[2], acc, kXcd, g);
       }
     }
   }
@@ -810,11 +815,16 @@ dplr_lr_status dispatch_order(dplr_lr_plan p, int64_t n_ion, const void* a, cons
 // and influence tables), sized for `cap` particles, taken in a fixed order
 // from get(&ptr, bytes, what): hipMalloc for plans, consecutive pieces of the
 // static scratch array for the no-allocation entry point.
+// share: the bin histograms, the spectra and the fields are placed in one
+// stretch as long as the histograms, the charge spectra, 3 field spectra and 3
+// unpadded field components (the size that decides which calls fit); the field
+// lies over the histograms and the charge spectra, which are not read any more
+// when it is written (plans keep the charge spectra for debug_copy).
 template <typename Get>
-dplr_lr_status carve_workspace(dplr_lr_plan p, size_t cap, Get&& get) {
+dplr_lr_status carve_workspace(dplr_lr_plan p, size_t cap, bool share, Get&& get) {
   const Geo& g = p->geo;
   const size_t ts = p->tsize, cs = 2 * ts;
-  const size_t nspec = (size_t)g.Kh * g.K[1] * g.K[2];
+  const size_t nspec = (size_t)g.Kh * g.K[1] * g.K[2], nyz = (size_t)g.K[1] * g.K[2];
   dplr_lr_status s2 = DPLR_LR_OK;
 #define DPLR_ALLOC(ptr, bytes, what)                                  \
   if (s2 == DPLR_LR_OK) {                                             \
@@ -826,17 +836,40 @@ dplr_lr_status carve_workspace(dplr_lr_plan p, size_t cap, Get&& get) {
   DPLR_ALLOC(p->bin_start, sizeof(int) * (g.nbins + 1), "bin_start");
   DPLR_ALLOC(p->bin_cursor, sizeof(int) * (g.nbins + 1), "bin_cursor");
   p->block_hist = (size_t)g.nbins * sizeof(int) <= std::min<size_t>(p->lds_budget, 65536);
-  if (p->block_hist) DPLR_ALLOC(p->bin_hist, sizeof(int) * (size_t)p->max_chunks * g.nbins, "bin histograms");
+  const size_t b_hist = p->block_hist ? sizeof(int) * (size_t)p->max_chunks * g.nbins : 0;
+  if (b_hist && !share) DPLR_ALLOC(p->bin_hist, b_hist, "bin histograms");
   DPLR_ALLOC(p->sorted, 4 * ts * cap, "sorted");
   DPLR_ALLOC(p->perm, sizeof(int) * cap, "perm");
   DPLR_ALLOC(p->sidx, sizeof(int) * cap, "stencil starts");
-  DPLR_ALLOC(p->spec, cs * nspec * g.nsplit, "spectrum (one partial per particle split)");
+  // one partial charge spectrum per particle split; A and B of the inverse z
+  // transform, or (separate inverse y and x passes) three field spectra; three
+  // field components in rows padded by P - 1 records, or (analytic
+  // differentiation) the potential in rows padded by kGatherAdPad
+  const bool ad = (p->cfg.flags & DPLR_LR_DIFF_AD) != 0;
+  const size_t b_spec = cs * nspec * g.nsplit, b_fspec = (p->ixy && p->nzout == 2 ? 2 : 3) * cs * nspec;
+  const size_t f_ik = 3 * (size_t)g.K[0], f_ad = (size_t)g.K[0] + kGatherAdPad;
+  const size_t f_pad = ad ? f_ad : f_ik + 3 * (size_t)(p->cfg.order - 1);
+  const size_t b_field = ts * (f_pad * nyz + kFieldTail);
+  if (share) {
+    auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const size_t total = al(b_hist) + al(b_spec) + al(3 * cs * nspec) + al(ts * std::max(f_ik, f_ad) * nyz);
+    unsigned char* base = nullptr;
+    DPLR_ALLOC(base, total, "histograms, spectra and fields");
+    // this fits for every mesh: the padding is 3 ts (P - 1) per field row, the
+    // charge spectra (Kx + 2) ts, and the histograms cover what rows of 16 lack
+    const size_t o_fspec = total - al(b_fspec);
+    if (s2 == DPLR_LR_OK && (o_fspec < al(b_hist) + b_spec || o_fspec < b_field))
+      return fail(p, DPLR_LR_E_UNSUPPORTED, "scratch layout");
+    if (b_hist) p->bin_hist = (int*)base;
+    p->spec = base + al(b_hist);
+    p->fspec = base + o_fspec;
+    p->field = base;
+  } else {
+    DPLR_ALLOC(p->spec, b_spec, "spectrum (one partial per particle split)");
+    DPLR_ALLOC(p->fspec, b_fspec, "field spectra");
+    DPLR_ALLOC(p->field, b_field, "fields");
+  }
   DPLR_ALLOC(p->qmax, sizeof(unsigned) * (size_t)std::max(p->max_chunks, 1), "charge maxima");
-  DPLR_ALLOC(p->fspec, 3 * cs * nspec, "field spectra");
-  // three interleaved field components, or (analytic differentiation) the
-  // potential in rows padded by kGatherAdPad
-  DPLR_ALLOC(p->field, ts * std::max<size_t>(3 * (size_t)g.K[0], (size_t)g.K[0] + kGatherAdPad) * g.K[1] * g.K[2],
-             "fields");
   DPLR_ALLOC(p->partials, sizeof(double) * 8 * g.nzblk, "partials");
 #undef DPLR_ALLOC
   return s2;
@@ -1025,7 +1058,7 @@ dplr_lr_status dplr_lr_plan_create(const dplr_lr_config* cfg, void* hip_stream, 
     p->G = (double*)t;
   }
   if (s2 == DPLR_LR_OK)
-    s2 = carve_workspace(p, (size_t)std::max<int64_t>(cfg->capacity, 1),
+    s2 = carve_workspace(p, (size_t)std::max<int64_t>(cfg->capacity, 1), false,
                          [p](void** ptr, size_t bytes, const char* what) { return alloc(p, ptr, bytes, what); });
   if (s2 != DPLR_LR_OK) {
     set_global_error(p->err);
@@ -1207,6 +1240,25 @@ dplr_lr_status dplr_lr_debug_copy(dplr_lr_plan p, int32_t which, void* dst, int6
                     : which == DPLR_LR_BUF_INFLUENCE ? (const void*)p->G
                     : which == DPLR_LR_BUF_Q32_CLAMPED ? (const void*)p->q32_clamped
                                                       : p->fspec;
+  if (which == DPLR_LR_BUF_FIELD_SPECTRA && p->nzout == 2) {
+    // the passes keep A and B, not the three products
+    const size_t cs = 2 * p->tsize;
+    const unsigned nb = (unsigned)(((size_t)bytes + 256 * cs - 1) / (256 * cs));
+    double sc[3] = {0.0, 0.0, 0.0};
+    if (p->has_box)
+      for (int a = 0; a < 3; ++a) sc[a] = 2.0 * M_PI / p->box[a];
+    if (nb > 0) {
+      if (p->fp64)
+        hipLaunchKernelGGL(k_field_spectra<double>, dim3(nb), dim3(256), 0, p->stream, (unsigned char*)dst,
+                           (const cpx<double>*)p->fspec, (size_t)bytes, p->ixy ? 1 : 0, p->geo, sc[0], sc[1], sc[2]);
+      else
+        hipLaunchKernelGGL(k_field_spectra<float>, dim3(nb), dim3(256), 0, p->stream, (unsigned char*)dst,
+                           (const cpx<float>*)p->fspec, (size_t)bytes, p->ixy ? 1 : 0, p->geo, sc[0], sc[1], sc[2]);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(p, e, "debug copy");
+    return DPLR_LR_OK;
+  }
   if (which == DPLR_LR_BUF_SPECTRUM && p->plane && p->geo.nsplit > 1) {
     // the plane spread leaves one partial spectrum per particle split: report their sum
     const size_t cs = 2 * p->tsize;
@@ -1390,11 +1442,13 @@ dplr_lr_status dplr_lr_compute_noalloc(const dplr_lr_config* cfg, const double b
     size_t need = off;
     dplr_lr_plan_s dry;
     dry.cfg = p->cfg; dry.fp64 = p->fp64; dry.tsize = p->tsize; dry.lds_budget = p->lds_budget; dry.geo = p->geo;
-    (void)carve_workspace(&dry, cap, [&need](void** ptr, size_t bytes, const char*) {
+    dry.ixy = p->ixy; dry.nzout = p->nzout;
+    st = carve_workspace(&dry, cap, true, [&need](void** ptr, size_t bytes, const char*) {
       *ptr = nullptr;
       need = align256(need + std::max<size_t>(bytes, 16));
       return DPLR_LR_OK;
     });
+    if (st != DPLR_LR_OK) return fail(nullptr, st, dry.err);
     if (need > kScratchBytes) {
       char msg[kErrLen];
       std::snprintf(msg, sizeof(msg),
@@ -1407,7 +1461,7 @@ dplr_lr_status dplr_lr_compute_noalloc(const dplr_lr_config* cfg, const double b
   p->twiddle = d.ptr + (p->fp64 ? kTwF32Bytes + sizeof(cpx<double>) * tw_entry(g.twN)
                                 : sizeof(cpx<float>) * tw_entry(g.twN));
   p->G = reinterpret_cast<double*>(d.ptr + g_off);
-  (void)carve_workspace(p, cap, [&](void** ptr, size_t bytes, const char*) {
+  (void)carve_workspace(p, cap, true, [&](void** ptr, size_t bytes, const char*) {
     *ptr = d.ptr + off;
     off = align256(off + std::max<size_t>(bytes, 16));
     return DPLR_LR_OK;

@@ -11,7 +11,14 @@
 //   spec     half spectrum [Kx/2+1][Kz][Ky] complex (y fastest); the spread
 //            writes one such partial spectrum per particle split; the pass
 //            after it adds them in split order.
-//   fspec    three field spectra [3][Kx/2+1][Kz][Ky] complex.
+//   fspec    spectra after the inverse z transform [.][Kx/2+1][Kz][Ky] complex:
+//            the three field components (FP32 plans whose planes fit in LDS),
+//            or A = -i G Q^ (its products with the integer indices n_x and n_y
+//            are the x and y field components) and B = -i n_z G Q^ (the z one)
+//            with the factors 2 pi / L_a applied to the forces.  Analytic
+//            differentiation keeps G Q^ alone.
+//   field    real fields in rows of Kx + P - 1 records (E_x, E_y, E_z), the last
+//            P - 1 repeating x = 0, 1, ..., so that no stencil row wraps in x.
 //   G        FP64 influence table [Kx/2+1][Ky/2+1][Kz/2+1] (G is even in
 //            every wave-vector component).
 #pragma once
@@ -50,21 +57,25 @@ struct PoissonConsts {
   double inv_4beta2;
 };
 
-constexpr int kEPT = 16;  // FFT elements per thread bound
+// FFT elements per thread: 16 FP32 complex values are 32 registers; FP64 rows
+// take 8, because 16 (64 registers before any temporary) spill under the 128
+// registers of a 1024-thread block.
+template <typename T>
+constexpr int fft_ept() { return sizeof(T) == 8 ? 8 : 16; }
 constexpr int kFftyThreads = 256;  // launch bound of the y pass
 
 // Copies n contiguous elements from global memory to LDS with U loads in
 // flight per thread before any of them is stored (a loop whose trip count
-// the compiler cannot see would otherwise wait for each load in turn).
+// the compiler cannot see would otherwise wait for each load in turn).  Loads
+// past the end repeat the last element: unconditional, so that the values stay
+// in registers (conditional loads of FP64 pairs went through scratch memory,
+// one wait each).
 template <int U, typename V>
 __device__ __forceinline__ void copy_g2s(V* __restrict__ dst, const V* __restrict__ src, int n) {
   for (int base = threadIdx.x; base < n; base += U * blockDim.x) {
     V r[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = base + u * blockDim.x;
-      if (e < n) r[u] = src[e];
-    }
+    for (int u = 0; u < U; ++u) r[u] = src[min(base + u * (int)blockDim.x, n - 1)];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = base + u * blockDim.x;
@@ -651,7 +662,7 @@ __global__ void __launch_bounds__(512) k_spread_fftx(const T4<T>* __restrict__ s
     __syncthreads();
   }
 
-  fft_rows<T, false, kEPT, true>(tile, nrc, Kx, RS, 1, false, tw, g.twN);
+  fft_rows<T, false, fft_ept<T>(), true>(tile, nrc, Kx, RS, 1, false, tw, g.twN);
 
   const int Kh = g.Kh;
   cpx<T>* sp_out = spec + (size_t)split * split_stride;
@@ -827,7 +838,7 @@ __global__ void __launch_bounds__(1024) k_spread_xy(const T4<T>* __restrict__ so
       }
     }
     __syncthreads();
-    fft_rows<T, false, kEPT, true>(tx_tile, Ky / 2, Kx, RS, 1, false, tw, g.twN);
+    fft_rows<T, false, fft_ept<T>(), true>(tx_tile, Ky / 2, Kx, RS, 1, false, tw, g.twN);
   }
 
   // y transform of the kx rows: the two half spectra of every row pair are
@@ -842,26 +853,49 @@ __global__ void __launch_bounds__(1024) k_spread_xy(const T4<T>* __restrict__ so
   };
   auto store_spec = [&](int k, int y, const cpx<T>& v) { out[(unsigned)imul(imul(k, Kz) + z, Ky) + y] = v; };
   if (fft_rows_io<T, false>(ty_tile, Kh, Ky, RY, tw, g.twN, each_elem(load_y), store_spec)) return;
+  // Otherwise in LDS.  FP64 transforms Kx/2 rows: the kx = 0 and Kx/2 terms of a
+  // real row are real, so row 0 carries them as real and imaginary part (one
+  // row fewer makes 8 elements per thread, the most that fit in registers),
+  // and its transform C(n) is taken apart as (C(n) + conj C(-n)) / 2 and
+  // (C(n) - conj C(-n)) / 2i.
+  constexpr bool kPack = sizeof(T) == 8;
+  const int KR = kPack ? Kx / 2 : Kh;
   {
-    constexpr int kMaxOut = 16;
+    constexpr int kMaxOut = fft_ept<T>();
     cpx<T> o[kMaxOut];
 #pragma unroll
     for (int c = 0; c < kMaxOut; ++c) {
       const int e = threadIdx.x + c * blockDim.x;  // e = kx * Ky + y
-      if (e < Kh * Ky) o[c] = load_y(e >> lky, e & (Ky - 1));
+      if (e < KR * Ky) {
+        const int k = e >> lky, y = e & (Ky - 1);
+        o[c] = load_y(k, y);
+        if (kPack && k == 0) o[c].y = load_y(KR, y).x;
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kMaxOut; ++c) {
       const int e = threadIdx.x + c * blockDim.x;
-      if (e < Kh * Ky) ty_tile[imul(e >> lky, RY) + lds_pad(e & (Ky - 1))] = o[c];
+      if (e < KR * Ky) ty_tile[imul(e >> lky, RY) + lds_pad(e & (Ky - 1))] = o[c];
     }
     __syncthreads();
   }
-  fft_rows<T, false, kEPT, true>(ty_tile, Kh, Ky, RY, 1, false, tw, g.twN);
+  fft_rows<T, false, fft_ept<T>(), true>(ty_tile, KR, Ky, RY, 1, false, tw, g.twN);
   for (int e = threadIdx.x; e < Kh * Ky; e += blockDim.x) {
     const int k = e >> lky, y = e & (Ky - 1);
-    out[(unsigned)imul(imul(k, Kz) + z, Ky) + y] = ty_tile[imul(k, RY) + lds_pad(y)];
+    cpx<T> v;
+    if (!kPack || (k > 0 && k < KR)) {
+      v = ty_tile[imul(k, RY) + lds_pad(y)];
+    } else {
+      const cpx<T> c1 = ty_tile[lds_pad(y)], c2 = cconj(ty_tile[lds_pad((Ky - y) & (Ky - 1))]);
+      if (k == 0) {
+        v = cpx<T>{(T)0.5 * (c1.x + c2.x), (T)0.5 * (c1.y + c2.y)};
+      } else {
+        const cpx<T> d = csub(c1, c2);
+        v = cpx<T>{(T)0.5 * d.y, (T)-0.5 * d.x};
+      }
+    }
+    out[(unsigned)imul(imul(k, Kz) + z, Ky) + y] = v;
   }
 }
 
@@ -876,12 +910,6 @@ __global__ void k_sum_partials(cpx<T>* __restrict__ dst, const cpx<T>* __restric
   dst[i] = a;
 }
 
-// ----------------------------------------------------------------------------
-// Transforms along y of contiguous blocks of zb rows (forward on the charge
-// spectrum, after adding the partial spectra of the particle splits; inverse on the
-// three field spectra).
-// Used forward on spec and inverse on the three field spectra.
-// ----------------------------------------------------------------------------
 // Final FP64 reduction of the z-pass partials with a fixed tree (bitwise
 // deterministic); run by block 0 of the inverse y pass, which follows the
 // z pass on the stream.
@@ -910,9 +938,19 @@ __device__ void reduce_partials(const double* __restrict__ partials, int nblk, d
   if (t >= 1 && t < 7 && virial) virial[t - 1] = pre * red[t * nt];
 }
 
+// ----------------------------------------------------------------------------
+// Transforms along y of contiguous blocks of zb rows of one kx plane, in place.
+// Forward (INV false): plane blockIdx / (Kz / zb) of the charge spectrum, after
+// adding the partial spectra of the particle splits.
+// Inverse: a block's rows of A (slot 0) give those of slot 1 (transform of
+// n_y A, the y component) and then, in place, of slot 0 (transform of A); rows
+// of slot 2 (B) are transformed in place.  With one component (analytic
+// differentiation) slot 0 is transformed in place.  Block 0 of the inverse
+// pass also performs the final energy/virial reduction.
+// ----------------------------------------------------------------------------
 template <typename T, bool INV>
-__global__ void __launch_bounds__(kFftyThreads) k_ffty(cpx<T>* __restrict__ data, const cpx<T>* __restrict__ twg, Geo g,
-                                              int nsum, size_t sum_stride,
+__global__ void __launch_bounds__(kFftyThreads) k_ffty(cpx<T>* __restrict__ data, int ncomp,
+                                              const cpx<T>* __restrict__ twg, Geo g, int nsum, size_t sum_stride,
                                               const double* __restrict__ partials, double pre,
                                               double* __restrict__ energy, double* __restrict__ virial) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -922,61 +960,91 @@ __global__ void __launch_bounds__(kFftyThreads) k_ffty(cpx<T>* __restrict__ data
   cpx<T>* tw = buf + g.zb * RS;
   const int nzb = Kz / g.zb;
   const int plane = blockIdx.x / nzb, zblk = blockIdx.x % nzb;
-  cpx<T>* base = data + ((size_t)plane * Kz + (size_t)zblk * g.zb) * Ky;
+  const size_t slot = (size_t)g.Kh * Kz * Ky;
+  const bool two = INV && ncomp == 3 && plane < g.Kh;  // rows of A
+  const int kx = plane < g.Kh ? plane : plane - g.Kh;
+  cpx<T>* base = data + (plane < g.Kh ? 0 : 2 * slot) + ((size_t)kx * Kz + (size_t)zblk * g.zb) * Ky;
   const int n = g.zb * Ky, lky = 31 - __clz(Ky);
-  for (int b0 = threadIdx.x; b0 < n; b0 += 16 * blockDim.x) {
-    cpx<T> r[16];
+  constexpr int E = fft_ept<T>();  // host: n <= E * blockDim.x
+  copy_g2s<8>(tw, twg, g.twN);
+  // A: first n_y A into slot 1, then A in place (its second read hits the cache)
+#pragma unroll 1  // two copies of the transform would need twice the registers
+  for (int pass = two ? 0 : 1; pass < 2; ++pass) {
+    // the element indices are formed again in each pass: kept across the
+    // transform, their addresses take twice the registers (249 instead of 132)
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    cpx<T> r[E];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = b0 + u * blockDim.x;
-      if (e < n) r[u] = base[e];
-    }
+    for (int u = 0; u < E; ++u) r[u] = base[min(t + u * (int)blockDim.x, n - 1)];
     // partial spectra of the other particle splits, added in split order
     for (int sp = 1; sp < nsum; ++sp) {
       const cpx<T>* ps = base + (size_t)sp * sum_stride;
+      cpx<T> q[E];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int e = b0 + u * blockDim.x;
-        if (e < n) r[u] = cadd(r[u], ps[e]);
+      for (int u = 0; u < E; ++u) q[u] = ps[min(t + u * (int)blockDim.x, n - 1)];
+#pragma unroll
+      for (int u = 0; u < E; ++u) r[u] = cadd(r[u], q[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+      const int e = t + u * (int)blockDim.x;
+      if (e < n) {
+        const int y = e & (Ky - 1);
+        cpx<T> v = r[u];
+        if (pass == 0) {
+          const T ny = (T)(2 * y < Ky ? y : 2 * y == Ky ? 0 : y - Ky);
+          v = cpx<T>{ny * v.x, ny * v.y};
+        }
+        buf[imul(e >> lky, RS) + lds_pad(y)] = v;
       }
     }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int e = b0 + u * blockDim.x;
-      if (e < n) buf[imul(e >> lky, RS) + lds_pad(e & (Ky - 1))] = r[u];
-    }
-  }
-  copy_g2s<8>(tw, twg, g.twN);
-  __syncthreads();
-  fft_rows<T, INV, kEPT, true>(buf, g.zb, Ky, RS, 1, false, tw, g.twN);
-  for (int e = threadIdx.x; e < n; e += blockDim.x) base[e] = buf[imul(e >> lky, RS) + lds_pad(e & (Ky - 1))];
-  if (INV && energy && blockIdx.x == 0) {
     __syncthreads();
-    reduce_partials(partials, g.nzblk, pre, energy, virial, reinterpret_cast<double*>(smem));
+    fft_rows<T, INV, E, true>(buf, g.zb, Ky, RS, 1, false, tw, g.twN);
+    cpx<T>* out = base + (pass == 0 ? slot : 0);
+    for (int e = t; e < n; e += blockDim.x) out[e] = buf[imul(e >> lky, RS) + lds_pad(e & (Ky - 1))];
+    __syncthreads();
   }
+  if (INV && energy && blockIdx.x == 0)
+    reduce_partials(partials, g.nzblk, pre, energy, virial, reinterpret_cast<double*>(smem));
 }
 
 // ----------------------------------------------------------------------------
-// Forward transform along z of yb columns of
-// one kx plane, the influence-function multiply with ik-differentiation, the
-// FP64 energy and virial partial sums, and the three inverse z transforms.
+// Forward transform along z of yb columns of one kx plane, the
+// influence-function multiply with ik-differentiation, the FP64 energy and
+// virial partial sums, and the inverse z transforms.
 //
-//   E^_a(n) = -i k'_a G(n) Q^(n),  k' = k with the Nyquist component zeroed;
+//   E^_a(n) = -i k'_a G(n) Q^(n),  k' = k with the Nyquist component zeroed.
+//   k'_x and k'_y are constant along a z column, so with nout = 2 the inverse
+//   z transform is taken of A = -i G Q^ (for x and y) and B = -i n'_z G Q^ (for
+//   z): two transforms and two spectra written instead of three (nout = 3).  The
+//   integer n' are exact in FP32; the passes that read A multiply by n'_x and
+//   n'_y.  nout = 2 pays where the transforms or the spectra are large: FP64 at
+//   128^3 (42.6 -> 29.3 us with the register change above) and FP32 at 256^3
+//   (124 -> 74 us, of which 3 -> 2 spectra is the larger part).  FP32 planes
+//   that fit in LDS keep three: at 128^3 the 1.6 us it saves here are lost to the
+//   factors in k_ifft_xy.  nout = 1: the potential spectrum G Q^.
 //   e  = sum w G |Q^|^2,  w = 1 on the kx = 0 and kx = Kx/2 planes, else 2;
 //   v_ab = sum w G |Q^|^2 (delta_ab - 2 (1 + k^2/(4 beta^2)) k_a k_b / k^2)
 //   (off-diagonal products use k', since full-spectrum terms with a Nyquist
 //   component cancel in +-n pairs).
+//
+// The pass waits on memory: every value of a column is needed before its first
+// butterfly.  So all 16 loads of a partial spectrum are in flight together
+// (one round trip per partial; one per value and partial took 35 us instead of
+// 16 on a 32^3 mesh of 8 partials, 24.3 instead of 21.0 at 128^3 with 2), and
+// the influence values are loaded before the forward transform.
 // ----------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict__ spec, int nsum, size_t sum_stride,
-                                                       int ncomp, cpx<T>* __restrict__ fspec,
+                                                       int nout, int bslot, cpx<T>* __restrict__ fspec,
                                                        const double* __restrict__ G, double* __restrict__ partials,
                                                        const cpx<T>* __restrict__ twg, Geo g, PoissonConsts pc) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2], Kh = g.Kh;
-  const int yb = g.yb, w3 = 3 * yb;
-  cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem);  // [Kz][3*yb]
-  cpx<T>* tw = buf + Kz * w3;
+  const int yb = g.yb, w2 = max(nout, 2) * yb;
+  cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem);  // [Kz][w2]
+  cpx<T>* tw = buf + Kz * w2;
   __shared__ double red[16][8];
 
   const int lyb = 31 - __clz(yb);  // yb is a power of two
@@ -992,12 +1060,22 @@ __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict_
   const int kx = blk / nyb, y0 = (blk - kx * nyb) << lyb;
   const unsigned col0 = (unsigned)imul(imul(kx, Kz), Ky) + y0;  // spec[kx][0][y0]
   const int n = Kz << lyb;                                      // elements (z, yl), yl fastest
+  const int Kyh = Ky / 2 + 1, Kzh = Kz / 2 + 1;
+  constexpr int U = 8;  // host: n <= U * blockDim.x
+  double Gr[U];
+  auto load_G = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * blockDim.x;
+      if (e < n) {
+        const int yl = e & (yb - 1), z = e >> lyb, ny = y0 + yl;
+        Gr[u] = G[(unsigned)imul(imul(kx, Kyh) + min(ny, Ky - ny), Kzh) + min(z, Kz - z)];
+      }
+    }
+  };
   // forward z transform of the yb columns, the partial spectra of the particle
   // splits added in split order on the way in
   copy_g2s<8>(tw, twg, g.twN);
-  // all 16 loads of a partial are in flight together: one round trip per
-  // partial instead of one per value and partial (35.2 us instead of 16.0 on a
-  // 32^3 mesh of 8 partials, 37 / 15.5 at 64^3, 24.3 / 21.0 at 128^3 with 2)
   auto load_s = [&](cpx<T> (&v)[16], int yl, auto elem) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = spec[col0 + imul(elem(i), Ky) + yl];
@@ -1010,102 +1088,94 @@ __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict_
       for (int i = 0; i < 16; ++i) v[i] = cadd(v[i], r[i]);
     }
   };
-  auto store_b = [&](int yl, int z, const cpx<T>& v) { buf[imul(z, w3) + yl] = v; };
-  if (!fft_cols_io<T, false>(buf, yb, Kz, w3, tw, g.twN, load_s, store_b)) {
-    for (int base = threadIdx.x; base < n; base += 8 * blockDim.x) {
-      cpx<T> r[8];
+  auto store_b = [&](int yl, int z, const cpx<T>& v) { buf[imul(z, w2) + yl] = v; };
+  load_G();
+  if (!fft_cols_io<T, false>(buf, yb, Kz, w2, tw, g.twN, load_s, store_b)) {
+    cpx<T> r[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = base + u * blockDim.x;
-        if (e < n) r[u] = spec[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))];
-      }
-      // partial spectra of the other particle splits, added in split order
-      for (int sp = 1; sp < nsum; ++sp) {
-        const cpx<T>* ps = spec + (size_t)sp * sum_stride;
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * blockDim.x;
+      if (e < n) r[u] = spec[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))];
+    }
+    // partial spectra of the other particle splits, added in split order
+    for (int sp = 1; sp < nsum; ++sp) {
+      const cpx<T>* ps = spec + (size_t)sp * sum_stride;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int e = base + u * blockDim.x;
-          if (e < n) r[u] = cadd(r[u], ps[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = base + u * blockDim.x;
-        if (e < n) buf[imul(e >> lyb, w3) + (e & (yb - 1))] = r[u];
+      for (int u = 0; u < U; ++u) {
+        const int e = threadIdx.x + u * blockDim.x;
+        if (e < n) r[u] = cadd(r[u], ps[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))]);
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * blockDim.x;
+      if (e < n) buf[imul(e >> lyb, w2) + (e & (yb - 1))] = r[u];
+    }
     __syncthreads();
-    fft_rows<T, false, kEPT>(buf, yb, Kz, 1, w3, true, tw, g.twN);
+    fft_rows<T, false, fft_ept<T>()>(buf, yb, Kz, 1, w2, true, tw, g.twN);
   }
 
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-  const int Kyh = Ky / 2 + 1, Kzh = Kz / 2 + 1;
   const double wgt = (kx == 0 || kx == Kx / 2) ? 1.0 : 2.0;
   const double kxv = pc.two_pi_over_L[0] * kx;
   const double kxd = (kx == Kx / 2) ? 0.0 : kxv;
-  for (int base = threadIdx.x; base < n; base += 8 * blockDim.x) {
-    double Gr[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = base + u * blockDim.x;
-      if (e < n) {
-        const int yl = e & (yb - 1), z = e >> lyb, ny = y0 + yl;
-        Gr[u] = G[(unsigned)imul(imul(kx, Kyh) + min(ny, Ky - ny), Kzh) + min(z, Kz - z)];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = base + u * blockDim.x;
-      if (e >= n) continue;
-      const int yl = e & (yb - 1), z = e >> lyb;
-      const int ny = y0 + yl;
-      const double kyv = pc.two_pi_over_L[1] * (ny <= Ky / 2 ? ny : ny - Ky);
-      const double kzv = pc.two_pi_over_L[2] * (z <= Kz / 2 ? z : z - Kz);
-      const double kyd = (2 * ny == Ky) ? 0.0 : kyv;
-      const double kzd = (2 * z == Kz) ? 0.0 : kzv;
-      const double Gv = Gr[u];
-      cpx<T>* bz = buf + imul(z, w3) + yl;
-      const cpx<T> q = bz[0];
-      const double s2 = (double)q.x * (double)q.x + (double)q.y * (double)q.y;
-      const double t = wgt * Gv * s2;
-      const double k2 = kxv * kxv + kyv * kyv + kzv * kzv;
-      const double c = (k2 > 0.0) ? 2.0 * (1.0 + k2 * pc.inv_4beta2) / k2 : 0.0;
-      acc[0] += t;
-      acc[1] += t * (1.0 - c * kxv * kxv);
-      acc[2] += t * (1.0 - c * kyv * kyv);
-      acc[3] += t * (1.0 - c * kzv * kzv);
-      acc[4] += t * (-c * kxd * kyd);
-      acc[5] += t * (-c * kxd * kzd);
-      acc[6] += t * (-c * kyd * kzd);
-      if (ncomp == 1) {
-        // analytic differentiation: the potential spectrum G Q^
-        const T gv = (T)Gv;
-        bz[0] = cpx<T>{gv * q.x, gv * q.y};
-      } else {
-        // -i k' G Q^ = k' G (q.y, -q.x)
-        const T gx = (T)(Gv * kxd), gy = (T)(Gv * kyd), gz = (T)(Gv * kzd);
-        bz[0] = cpx<T>{gx * q.y, -gx * q.x};
-        bz[yb] = cpx<T>{gy * q.y, -gy * q.x};
-        bz[2 * yb] = cpx<T>{gz * q.y, -gz * q.x};
-      }
+  for (int u = 0; u < U; ++u) {
+    const int e = threadIdx.x + u * blockDim.x;
+    if (e >= n) continue;
+    const int yl = e & (yb - 1), z = e >> lyb;
+    const int ny = y0 + yl;
+    const int nz = z <= Kz / 2 ? z : z - Kz;
+    const double kyv = pc.two_pi_over_L[1] * (ny <= Ky / 2 ? ny : ny - Ky);
+    const double kzv = pc.two_pi_over_L[2] * nz;
+    const double kyd = (2 * ny == Ky) ? 0.0 : kyv;
+    const double kzd = (2 * z == Kz) ? 0.0 : kzv;
+    const double Gv = Gr[u];
+    cpx<T>* bz = buf + imul(z, w2) + yl;
+    const cpx<T> q = bz[0];
+    const double s2 = (double)q.x * (double)q.x + (double)q.y * (double)q.y;
+    const double t = wgt * Gv * s2;
+    const double k2 = kxv * kxv + kyv * kyv + kzv * kzv;
+    const double c = (k2 > 0.0) ? 2.0 * (1.0 + k2 * pc.inv_4beta2) / k2 : 0.0;
+    acc[0] += t;
+    acc[1] += t * (1.0 - c * kxv * kxv);
+    acc[2] += t * (1.0 - c * kyv * kyv);
+    acc[3] += t * (1.0 - c * kzv * kzv);
+    acc[4] += t * (-c * kxd * kyd);
+    acc[5] += t * (-c * kxd * kzd);
+    acc[6] += t * (-c * kyd * kzd);
+    const T gv = (T)Gv;
+    if (nout == 1) {
+      // analytic differentiation: the potential spectrum G Q^
+      bz[0] = cpx<T>{gv * q.x, gv * q.y};
+    } else if (nout == 3) {
+      // -i k' G Q^ = k' G (q.y, -q.x)
+      const T gx = (T)(Gv * kxd), gy = (T)(Gv * kyd), gz = (T)(Gv * kzd);
+      bz[0] = cpx<T>{gx * q.y, -gx * q.x};
+      bz[yb] = cpx<T>{gy * q.y, -gy * q.x};
+      bz[2 * yb] = cpx<T>{gz * q.y, -gz * q.x};
+    } else {
+      // -i f Q^ = f (q.y, -q.x) with f = G and n'_z G
+      const T gz = (T)(Gv * (double)((2 * z == Kz) ? 0 : nz));
+      bz[0] = cpx<T>{gv * q.y, -gv * q.x};
+      bz[yb] = cpx<T>{gz * q.y, -gz * q.x};
     }
   }
   __syncthreads();
-  // ncomp inverse z transforms (three field components, or the potential);
-  // the fused form writes the spectra directly
-  const unsigned fstride = (unsigned)imul(imul(Kh, Kz), Ky);
+  // inverse z transforms; the fused form writes the spectra directly
+  const unsigned fstride = (unsigned)imul(imul(Kh, Kz), Ky) * (unsigned)bslot;
   auto store_f = [&](int c, int z, const cpx<T>& v) {
     const int a = c >> lyb, yl = c & (yb - 1);  // column c = a * yb + yl
     fspec[a * fstride + col0 + imul(z, Ky) + yl] = v;
   };
-  auto load_b = [&](int c, int z) { return buf[imul(z, w3) + c]; };
-  if (!fft_cols_io<T, true>(buf, ncomp * yb, Kz, w3, tw, g.twN, each_elem(load_b), store_f)) {
-    fft_rows<T, true, kEPT>(buf, ncomp * yb, Kz, 1, w3, true, tw, g.twN);
-    // store: e = ((z * ncomp + a) << lyb) + yl
-    for (int e = threadIdx.x; e < ncomp * n; e += blockDim.x) {
+  auto load_b = [&](int c, int z) { return buf[imul(z, w2) + c]; };
+  if (!fft_cols_io<T, true>(buf, nout * yb, Kz, w2, tw, g.twN, each_elem(load_b), store_f)) {
+    fft_rows<T, true, fft_ept<T>()>(buf, nout * yb, Kz, 1, w2, true, tw, g.twN);
+    // store: e = ((z * nout + a) << lyb) + yl
+    for (int e = threadIdx.x; e < nout * n; e += blockDim.x) {
       const int za = e >> lyb, yl = e & (yb - 1);
-      const int z = za / ncomp, a = za - ncomp * z;
-      fspec[a * fstride + col0 + imul(z, Ky) + yl] = buf[imul(z, w3) + imul(a, yb) + yl];
+      const int z = za / nout, a = za - nout * z;
+      fspec[a * fstride + col0 + imul(z, Ky) + yl] = buf[imul(z, w2) + imul(a, yb) + yl];
     }
   }
 
@@ -1126,17 +1196,36 @@ __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict_
   }
 }
 
-// ----------------------------------------------------------------------------
-// Inverse complex-to-real transform along x of the three field spectra.  A
-// workgroup takes one z plane and yb consecutive y rows of all three fields
-// (3 * yb real rows, transformed in pairs as complex rows) and writes the
-// real fields interleaved, E[z][y][x] = (Ex, Ey, Ez), so the gather reads one
-// 3-component record per stencil point.
-// ----------------------------------------------------------------------------
-#ifndef DPLR_GATHER_OCC
-#define DPLR_GATHER_OCC
-#endif
+// The field spectra E^_a of the last call from A and B (inspection copy): ik
+// component a of element e is scale_a n' times A or B (slot 1 already carries
+// n'_y after a separate inverse y pass).  `bytes` of the result.
+template <typename T>
+__global__ void k_field_spectra(unsigned char* __restrict__ dst, const cpx<T>* __restrict__ fspec, size_t bytes,
+                                int ixy, Geo g, double s0, double s1, double s2) {
+  const size_t nspec = (size_t)g.Kh * g.K[1] * g.K[2];
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i * sizeof(cpx<T>) >= bytes) return;
+  const int a = (int)(i / nspec);
+  const size_t e = i - a * nspec;
+  const int ny = (int)(e % g.K[1]), kx = (int)(e / ((size_t)g.K[1] * g.K[2]));
+  const size_t slot = ixy ? (a == 2 ? 1 : 0) : a;
+  const cpx<T> v = fspec[slot * nspec + e];
+  double f = a == 0 ? s0 * (2 * kx == g.K[0] ? 0 : kx) : a == 1 ? s1 : s2;
+  if (a == 1 && ixy) f *= 2 * ny < g.K[1] ? ny : 2 * ny == g.K[1] ? 0 : ny - g.K[1];
+  const cpx<T> o{(T)(f * (double)v.x), (T)(f * (double)v.y)};
+  const unsigned char* ob = reinterpret_cast<const unsigned char*>(&o);
+  const size_t left = bytes - i * sizeof(cpx<T>);
+  for (size_t b = 0; b < sizeof(cpx<T>) && b < left; ++b) dst[i * sizeof(cpx<T>) + b] = ob[b];
+}
 
+// ----------------------------------------------------------------------------
+// Inverse complex-to-real transform along x of the three field spectra (the x
+// component's is n'_x times slot 0).  A workgroup takes one z plane and yb
+// consecutive y rows of all three fields (3 * yb real rows, transformed in
+// pairs as complex rows) and writes the real fields interleaved,
+// E[z][y][x] = (Ex, Ey, Ez), so the gather reads one 3-component record per
+// stencil point.
+// ----------------------------------------------------------------------------
 template <typename T>
 struct F3 {
   T x, y, z;
@@ -1147,12 +1236,12 @@ struct F3 {
 // (and keeps rows 16-byte aligned)
 constexpr int kGatherAdPad = 8;
 
-// ncomp = 3 writes the interleaved field records; ncomp = 1 (analytic
-// differentiation) writes the potential in rows of Kx + kGatherAdPad values,
-// the last ones repeating x = 0, 1, ...
+// ncomp = 3 writes the interleaved field records, ncomp = 1 (analytic
+// differentiation) the potential; rows of Kx + xpad, the last ones repeating
+// x = 0, 1, ...
 template <typename T>
 __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec, T* __restrict__ field, int ncomp,
-                                               const cpx<T>* __restrict__ twg, Geo g) {
+                                               int xpad, const cpx<T>* __restrict__ twg, Geo g) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2], Kh = g.Kh;
   const int yb = g.xyb;                  // y rows per block
@@ -1172,6 +1261,7 @@ __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec,
     const cpx<T>* s0 = fspec + (size_t)(r0 / yb) * fstride + (size_t)z * Ky + y0 + r0 % yb;
     const cpx<T>* s1 = fspec + (size_t)(r1 / yb) * fstride + (size_t)z * Ky + y0 + r1 % yb;
     cpx<T>* zr = tile + imul(c_t, RS);
+    const bool xcomp = ncomp == 3 && r0 < yb;
     for (int kb = k_t; kb < Kh; kb += 4 * kstep) {
       cpx<T> A[4], B[4];
 #pragma unroll
@@ -1185,6 +1275,11 @@ __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec,
         if (kk < Kh) {
           cpx<T> av = A[u], bv = B[u];
           if (kk == 0 || kk == Kx / 2) { av.y = (T)0; bv.y = (T)0; }
+          if (xcomp) {
+            const T nx = (T)(kk == Kx / 2 ? 0 : kk);
+            av = cpx<T>{nx * av.x, nx * av.y};
+            bv = cpx<T>{nx * bv.x, nx * bv.y};
+          }
           zr[lds_pad(kk)] = cpx<T>{av.x - bv.y, av.y + bv.x};
           if (kk > 0 && kk < Kx / 2) zr[lds_pad(Kx - kk)] = cpx<T>{av.x + bv.y, bv.x - av.y};
         }
@@ -1192,33 +1287,25 @@ __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec,
     }
   }
   __syncthreads();
-  fft_rows<T, true, kEPT, true>(tile, nrc, Kx, RS, 1, false, tw, g.twN);
+  fft_rows<T, true, fft_ept<T>(), true>(tile, nrc, Kx, RS, 1, false, tw, g.twN);
 
   // store: record (yl, x) gathers component a from row r = a*yb + yl
   const T* tr = reinterpret_cast<const T*>(tile);
   const int lkx = 31 - __clz(Kx);
-  if (ncomp == 3) {
-    F3<T>* out = reinterpret_cast<F3<T>*>(field) + ((size_t)z * Ky + y0) * Kx;
-    for (int e = threadIdx.x; e < yb * Kx; e += blockDim.x) {
-      const int yl = e >> lkx, x = e & (Kx - 1);
-      const int col = 2 * lds_pad(x);
-      T v[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int r = a * yb + yl;
-        v[a] = tr[2 * imul(r >> 1, RS) + col + (r & 1)];
-      }
-      out[e] = F3<T>{v[0], v[1], v[2]};
-    }
-  } else {
-    const int RX = Kx + kGatherAdPad;
-    T* out = field + ((size_t)z * Ky + y0) * RX;
-    for (int e = threadIdx.x; e < yb * Kx; e += blockDim.x) {
-      const int yl = e >> lkx, x = e & (Kx - 1);
-      const T v = tr[2 * imul(yl >> 1, RS) + 2 * lds_pad(x) + (yl & 1)];
-      out[imul(yl, RX) + x] = v;
-      if (x < kGatherAdPad) out[imul(yl, RX) + Kx + x] = v;
-    }
+  const int RX = Kx + xpad;
+  auto value = [&](int a, int yl, int x) {
+    const int r = a * yb + yl;
+    return tr[2 * (imul(r >> 1, RS) + lds_pad(x)) + (r & 1)];
+  };
+  auto put = [&](int yl, int x, int xo) {
+    const size_t o = ((size_t)z * Ky + y0) * RX + imul(yl, RX) + xo;
+    if (ncomp == 3) reinterpret_cast<F3<T>*>(field)[o] = F3<T>{value(0, yl, x), value(1, yl, x), value(2, yl, x)};
+    else field[o] = value(0, yl, x);
+  };
+  for (int e = threadIdx.x; e < yb * Kx; e += blockDim.x) put(e >> lkx, e & (Kx - 1), e & (Kx - 1));
+  for (int e = threadIdx.x; e < yb * xpad; e += blockDim.x) {
+    const int yl = e / xpad, x = e - yl * xpad;
+    put(yl, x, Kx + x);
   }
 }
 
@@ -1229,13 +1316,18 @@ __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec,
 // recombined into complex pairs of real x rows: row pair (2c, 2c+1) takes
 // A + iB for kx <= Kx/2 and conj(A) + i conj(B) at Kx - kx (Hermitian
 // symmetry), with the imaginary parts of the kx = 0 and Kx/2 terms dropped.
+// FP64 reads A times n'_x, A times n'_y or B, and as the kx = 0 and Kx/2 rows
+// are real after the y transform it carries them as real and imaginary part of
+// one row: Kx/2 rows are 8 elements per thread of a 1024-thread block, Kx/2 + 1
+// would be 9 and spill.
 // One inverse complex FFT per pair along x gives both real rows, written as
 // component a of the interleaved field records (ncomp = 3 field components
 // for ik differentiation, ncomp = 1 for the potential of analytic
 // differentiation).  Block b serves plane z = 8 (b / (8 ncomp)) + b % 8 and
 // component (b / 8) % ncomp, so the components of a plane land on the same XCD
-// (blocks are dealt round-robin over 8 XCDs) and its L2 merges their partial
-// record writes.  Block 0 also performs the final energy/virial reduction.
+// (blocks are dealt round-robin over 8 XCDs): its L2 serves the second read of
+// A and merges the partial record writes.  Block 0 also performs the final
+// energy/virial reduction.
 // ----------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fspec, T* __restrict__ field,
@@ -1243,12 +1335,14 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
                                                   const double* __restrict__ partials, double pre,
                                                   double* __restrict__ energy, double* __restrict__ virial) {
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool kPack = sizeof(T) == 8;
   const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2], Kh = g.Kh;
-  const int RS = padded_len(Kx) + 1;  // x rows (complex pairs of real rows)
-  const int RY = padded_len(Ky) + 1;  // y rows ([kx][y])
-  cpx<T>* ty = reinterpret_cast<cpx<T>*>(smem);  // [Kh][RY]
+  const int KR = kPack ? Kx / 2 : Kh;  // rows transformed along y
+  const int RS = padded_len(Kx) + 1;   // x rows (complex pairs of real rows)
+  const int RY = padded_len(Ky) + 1;   // y rows ([kx][y])
+  cpx<T>* ty = reinterpret_cast<cpx<T>*>(smem);  // [KR][RY]
   cpx<T>* tx = reinterpret_cast<cpx<T>*>(smem);  // [Ky/2][RS]
-  const size_t b_ty = (size_t)Kh * RY * sizeof(cpx<T>);
+  const size_t b_ty = (size_t)KR * RY * sizeof(cpx<T>);
   const size_t b_tx = (size_t)(Ky / 2) * RS * sizeof(cpx<T>);
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem + max(b_ty, b_tx));
   const int zx = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -1259,25 +1353,39 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
 
   // rows (kx, z) of component a: Ky contiguous values each, Kz * Ky apart.
   // The fused form loads them straight into the transform's registers.
-  constexpr int kMax = 16;  // host: Kh * Ky <= 16 * blockDim.x
-  const cpx<T>* src = fspec + (size_t)a * Kh * Kz * Ky + (size_t)z * Ky;
+  constexpr int kMax = fft_ept<T>();  // host: KR * Ky <= kMax * blockDim.x
   const size_t rstride = (size_t)Kz * Ky;
+  const cpx<T>* src = fspec + (size_t)(kPack ? (a == 2 ? 1 : 0) : a) * Kh * rstride + (size_t)z * Ky;
   auto load_g = [&](int k, int y) { return src[(size_t)k * rstride + y]; };
   auto store_ty = [&](int k, int y, const cpx<T>& v) { ty[imul(k, RY) + lds_pad(y)] = v; };
-  if (!fft_rows_io<T, true>(ty, Kh, Ky, RY, tw, g.twN, each_elem(load_g), store_ty)) {
+  if (!fft_rows_io<T, true>(ty, KR, Ky, RY, tw, g.twN, each_elem(load_g), store_ty)) {
     cpx<T> r[kMax];
 #pragma unroll
     for (int c = 0; c < kMax; ++c) {
       const int e = threadIdx.x + c * blockDim.x;
-      if (e < Kh * Ky) r[c] = load_g(e >> lky, e & (Ky - 1));
+      if (e < KR * Ky) r[c] = load_g(e >> lky, e & (Ky - 1));
     }
 #pragma unroll
     for (int c = 0; c < kMax; ++c) {
       const int e = threadIdx.x + c * blockDim.x;
-      if (e < Kh * Ky) store_ty(e >> lky, e & (Ky - 1), r[c]);
+      if (e < KR * Ky) {
+        const int k = e >> lky, y = e & (Ky - 1);
+        cpx<T> v = r[c];
+        if (kPack) {
+          // n'_x, n'_y or 1 (with n'_x = 0 for kx = 0 and Kx/2)
+          const int ny = 2 * y < Ky ? y : 2 * y == Ky ? 0 : y - Ky;
+          const T f = (T)(ncomp == 1 || a == 2 ? 1 : a == 0 ? k : ny);
+          v = cpx<T>{f * v.x, f * v.y};
+          if (k == 0) {  // F_0 + i F_{Kx/2}
+            const cpx<T> w = load_g(KR, y);
+            v = cpx<T>{v.x - f * w.y, v.y + f * w.x};
+          }
+        }
+        store_ty(k, y, v);
+      }
     }
     __syncthreads();
-    fft_rows<T, true, kEPT, true>(ty, Kh, Ky, RY, 1, false, tw, g.twN);
+    fft_rows<T, true, kMax, true>(ty, KR, Ky, RY, 1, false, tw, g.twN);
   }
 
   // complex row pairs along x: pair pr takes A + iB (A, B: rows 2pr, 2pr+1)
@@ -1286,41 +1394,28 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
   auto load_r = [&](int pr, int m) {
     const bool up = m > Kx / 2;
     const int k = up ? Kx - m : m;
-    const cpx<T>* row = ty + imul(k, RY);
+    const cpx<T>* row = ty + imul(kPack && k == Kx / 2 ? 0 : k, RY);
     cpx<T> av = row[lds_pad(2 * pr)], bv = row[lds_pad(2 * pr + 1)];
+    if (kPack && k == Kx / 2) { av.x = av.y; bv.x = bv.y; }
     if (k == 0 || k == Kx / 2) { av.y = (T)0; bv.y = (T)0; }
     return up ? cpx<T>{av.x + bv.y, bv.x - av.y} : cpx<T>{av.x - bv.y, av.y + bv.x};
   };
   auto store_tx = [&](int pr, int x, const cpx<T>& v) { tx[imul(pr, RS) + lds_pad(x)] = v; };
   if (!fft_rows_io<T, true>(tx, Ky / 2, Kx, RS, tw, g.twN, each_elem(load_r), store_tx)) {
-    const int half = Ky >> 1, lhalf = lky - 1;
-    constexpr int kPairs = kMax / 2;  // Kh * Ky / 2 <= 8 * blockDim.x
-    cpx<T> A[kPairs], B[kPairs];
+    cpx<T> r[kMax];  // (Ky / 2) Kx elements
 #pragma unroll
-    for (int c = 0; c < kPairs; ++c) {
-      const int i = threadIdx.x + c * blockDim.x;  // i = kx * (Ky/2) + pair
-      if (i < Kh * half) {
-        const int k = i >> lhalf, pr = i & (half - 1);
-        const cpx<T>* row = ty + imul(k, RY);
-        A[c] = row[lds_pad(2 * pr)];
-        B[c] = row[lds_pad(2 * pr + 1)];
-      }
+    for (int c = 0; c < kMax; ++c) {
+      const int e = threadIdx.x + c * blockDim.x;
+      if (e < (Ky / 2) * Kx) r[c] = load_r(e >> lkx, e & (Kx - 1));
     }
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < kPairs; ++c) {
-      const int i = threadIdx.x + c * blockDim.x;
-      if (i < Kh * half) {
-        const int k = i >> lhalf, pr = i & (half - 1);
-        cpx<T> av = A[c], bv = B[c];
-        if (k == 0 || k == Kx / 2) { av.y = (T)0; bv.y = (T)0; }
-        cpx<T>* zr = tx + imul(pr, RS);
-        zr[lds_pad(k)] = cpx<T>{av.x - bv.y, av.y + bv.x};
-        if (k > 0 && k < Kx / 2) zr[lds_pad(Kx - k)] = cpx<T>{av.x + bv.y, bv.x - av.y};
-      }
+    for (int c = 0; c < kMax; ++c) {
+      const int e = threadIdx.x + c * blockDim.x;
+      if (e < (Ky / 2) * Kx) store_tx(e >> lkx, e & (Kx - 1), r[c]);
     }
     __syncthreads();
-    fft_rows<T, true, kEPT, true>(tx, Ky / 2, Kx, RS, 1, false, tw, g.twN);
+    fft_rows<T, true, kMax, true>(tx, Ky / 2, Kx, RS, 1, false, tw, g.twN);
   }
 
   // real rows (y even in the real parts, y odd in the imaginary parts) to
@@ -1334,7 +1429,12 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
     const int y = e >> lkx, x = e & (Kx - 1);
     const T v = tr[2 * (imul(y >> 1, RS) + lds_pad(x)) + (y & 1)];
     out[(size_t)(imul(y, RX) + x) * ncomp] = v;
-    if (x < xpad) out[(size_t)(imul(y, RX) + Kx + x) * ncomp] = v;
+  }
+  // the repeated records in a loop of their own: a store under x < xpad above
+  // would be issued by half of the waves' iterations
+  for (int e = threadIdx.x; e < imul(Ky, xpad); e += blockDim.x) {
+    const int y = e / xpad, x = e - y * xpad;
+    out[(size_t)(imul(y, RX) + Kx + x) * ncomp] = tr[2 * (imul(y >> 1, RS) + lds_pad(x)) + (y & 1)];
   }
   if (energy && blockIdx.x == 0) {
     __syncthreads();
@@ -1344,91 +1444,155 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
 
 // ----------------------------------------------------------------------------
 // Force interpolation with the assignment weights of the spread, reading the
-// real fields from memory (L1/L2).  P lanes serve one particle: lane tx reads
-// the column s_x + tx of all P x P (y, z) rows, so each group's loads cover
-// P consecutive records; the P partial sums are then added across the group.
+// real fields from memory (L1/L2).  A stencil row is 3 P consecutive values
+// (P records of three components); its rows are read as 16-byte pieces, one per
+// lane, so L = ceil(3 P / C) lanes serve one particle (C values a piece: 4 in
+// FP32, 2 in FP64) and a row never wraps (the field rows are padded).  Lane t
+// holds values C t .. C t + C - 1, sums each over the P x P rows with the y and
+// z weights, and only then applies the x weights of the one or two records
+// that its values belong to and sorts them into components.
+// The kernel is bound by the 64-byte lines that the L1 looks up, one a cycle:
+// with one lane per stencil column (12 bytes a lane, 5 lanes a particle at
+// order 5) the hardware's groups of 16 lanes straddled particles and took 64
+// look-ups per particle; four lanes of 16 bytes keep particles whole (about
+// 48).  72,192 waters at 128^3: 33.9 -> 30.5 us (order 5), 63 -> 53 us (FP64);
+// 1.2 M charges at 256^3: 188 -> 178 us.
 // Blocks walk the sorted particles in order, and consecutive chunks are
 // mapped to the same XCD so each XCD's L2 serves one slab of the field.
 // ----------------------------------------------------------------------------
 template <typename T, int P>
-__global__ void __launch_bounds__(256) DPLR_GATHER_OCC k_gather(const F3<T>* __restrict__ field, const T4<T>* __restrict__ sorted,
+struct GatherSplit {
+  static constexpr int C = 16 / (int)sizeof(T);    // values per lane
+  static constexpr int L = (3 * P + C - 1) / C;    // lanes per particle
+  static constexpr int GPW = 64 / L;               // particles per wave
+  static constexpr int kPerBlock = 4 * GPW;        // blocks of 4 waves
+};
+// Values that a piece of the last row may reach beyond the field.
+constexpr int kFieldTail = 4;
+
+template <typename T>
+struct Piece;
+template <>
+struct Piece<float> {
+  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct Piece<double> {
+  typedef double V __attribute__((ext_vector_type(2), aligned(8)));
+};
+
+// The force of one particle: its L lanes (lane t of the group that starts at
+// wave lane gbase) read the stencil at (sx, sy, sz) of the field rows of RX
+// records; component a is multiplied by qx, qy, qz (charge and units).  Every
+// lane of the wave calls it; all lanes of the group return the sums.
+template <typename T, int P>
+__device__ __forceinline__ void gather_field(const T* __restrict__ field, int RX, int Ky, int Kz, int sx, int sy,
+                                             int sz, T dx, T dy, T dz, T qx, T qy, T qz, int t, int gbase, bool on,
+                                             T (&tot)[3]) {
+  constexpr int C = GatherSplit<T, P>::C, L = GatherSplit<T, P>::L;
+  T val[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) val[c] = (T)0;
+  if (on) {
+    T wy[P], wz[P];
+    bspline_weights<T, P>(dy, wy);
+    bspline_weights<T, P>(dz, wz);
+    T acc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = (T)0;
+    unsigned row[P];
+#pragma unroll
+    for (int ty = 0; ty < P; ++ty) {
+      int gy = sy + ty;
+      if (gy >= Ky) gy -= Ky;
+      row[ty] = (unsigned)imul(imul(gy, RX) + sx, 3) + C * t;
+    }
+    const unsigned pstride = (unsigned)imul(imul(Ky, RX), 3);
+    // all loads of a batch of z planes are issued before any of them is used
+    // (memory-level parallelism: the loop is latency bound otherwise)
+    constexpr int TZB = (P <= 5) ? P : ((P <= 6) ? 3 : 2);
+    typedef typename Piece<T>::V V;
+#pragma unroll
+    for (int tz0 = 0; tz0 < P; tz0 += TZB) {
+      V r[TZB][P];
+#pragma unroll
+      for (int b = 0; b < TZB; ++b) {
+        if (tz0 + b < P) {
+          int gz = sz + tz0 + b;
+          if (gz >= Kz) gz -= Kz;
+          const T* pl = field + (size_t)gz * pstride;
+#pragma unroll
+          for (int ty = 0; ty < P; ++ty) r[b][ty] = *reinterpret_cast<const V*>(pl + row[ty]);
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < TZB; ++b) {
+        if (tz0 + b < P) {
+#pragma unroll
+          for (int ty = 0; ty < P; ++ty) {
+            const T w = wz[tz0 + b] * wy[ty];
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] += w * r[b][ty][c];
+          }
+        }
+      }
+    }
+    // value C t + c belongs to record (C t + c) / 3, component (C t + c) % 3;
+    // values past the stencil (the last lane) are not read below
+    T wx[P];
+    bspline_weights<T, P>(dx, wx);
+    const int v0 = C * t, r0 = (int)(((unsigned)v0 * 43691u) >> 17), m0 = v0 - 3 * r0;  // v0 / 3 for v0 < 2^15
+    T wa = (T)0, wb = (T)0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      wa = (r0 == q) ? wx[q] : wa;
+      wb = (r0 + 1 == q) ? wx[q] : wb;
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int m = m0 + c;  // < 6
+      const int comp = m < 3 ? m : m - 3;
+      val[c] = ((comp == 0 ? qx : comp == 1 ? qy : qz) * (m < 3 ? wa : wb)) * acc[c];
+    }
+  }
+  // sum over the stencil columns in order
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    T s = (T)0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) s += __shfl(val[(3 * q + a) % C], gbase + (3 * q + a) / C, 64);
+    tot[a] = s;
+  }
+}
+
+// fx, fy, fz: k_e / V, times 2 pi / L_a where the spectra carry integer indices.
+template <typename T, int P>
+__global__ void __launch_bounds__(256) k_gather(const T* __restrict__ field, const T4<T>* __restrict__ sorted,
                                                 const int* __restrict__ sidx, const int* __restrict__ perm,
                                                 int n, int nchunks, T* __restrict__ ion_f, T* __restrict__ wc_f,
-                                                int64_t n_ion, T fscale, int accumulate, int nxcd, Geo g) {
-  const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2];
-  constexpr int GPW = 64 / P;
+                                                int64_t n_ion, T fx, T fy, T fz, int accumulate, int nxcd, Geo g) {
+  typedef GatherSplit<T, P> S;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int grp = lane / P, tx = lane - grp * P;
-  const bool lane_on = grp < GPW;
-  const int per_block = (blockDim.x >> 6) * GPW;
+  const int grp = lane / S::L, t = lane - grp * S::L;
   // XCD-aware order: blocks b, b + nxcd, ... run on one XCD; give them
   // consecutive chunks of the sorted particles.  The grid is a multiple of
   // nxcd, so b -> chunk is a bijection onto [0, gridDim.x); chunks at or
   // beyond nchunks hold no particles.
   const int per_xcd = gridDim.x / nxcd;
   const int chunk = (blockIdx.x % nxcd) * per_xcd + blockIdx.x / nxcd;
-  const int v = chunk * per_block + wave * GPW + grp;
-  const bool on = lane_on && chunk < nchunks && v < n;
-  T part[3] = {(T)0, (T)0, (T)0};
-  T qw = (T)0;
-  int src = 0;
+  const int v = chunk * S::kPerBlock + wave * S::GPW + grp;
+  const bool on = grp < S::GPW && chunk < nchunks && v < n;
+  T4<T> pt{(T)0, (T)0, (T)0, (T)0};
+  int sp = 0, src = 0;
   if (on) {
-    const T4<T> pt = sorted[v];
-    const int sp = sidx[v];
+    pt = sorted[v];
+    sp = sidx[v];
     src = perm[v];
-    const int sx = sp & 1023, sy = (sp >> 10) & 1023, sz = sp >> 20;
-    T wy[P], wz[P], wxt, dxt;
-    bspline_weight_at<T, P>(pt.x, tx, wxt, dxt);  // this lane's column only
-    bspline_weights<T, P>(pt.y, wy);
-    bspline_weights<T, P>(pt.z, wz);
-    int gx = sx + tx;
-    if (gx >= Kx) gx -= Kx;
-    // all loads of a batch of z planes are issued before any of them is used
-    // (memory-level parallelism: the loop is latency bound otherwise)
-    constexpr int TZB = (P <= 5) ? P : ((P <= 6) ? 3 : 2);
-#pragma unroll
-    for (int tz0 = 0; tz0 < P; tz0 += TZB) {
-      F3<T> r[TZB][P];
-#pragma unroll
-      for (int dz = 0; dz < TZB; ++dz) {
-        if (tz0 + dz < P) {
-          int gz = sz + tz0 + dz;
-          if (gz >= Kz) gz -= Kz;
-          const F3<T>* fz = field + (unsigned)imul(gz, Ky) * (unsigned)Kx + gx;
-#pragma unroll
-          for (int ty = 0; ty < P; ++ty) {
-            int gy = sy + ty;
-            if (gy >= Ky) gy -= Ky;
-            r[dz][ty] = fz[imul(gy, Kx)];
-          }
-        }
-      }
-#pragma unroll
-      for (int dz = 0; dz < TZB; ++dz) {
-        if (tz0 + dz < P) {
-#pragma unroll
-          for (int ty = 0; ty < P; ++ty) {
-            const T w = wz[tz0 + dz] * wy[ty];
-            part[0] += w * r[dz][ty].x;
-            part[1] += w * r[dz][ty].y;
-            part[2] += w * r[dz][ty].z;
-          }
-        }
-      }
-    }
-    qw = fscale * pt.w * wxt;
   }
-  const int gbase = grp * P;
   T tot[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const T mine = qw * part[a];
-    T s = (T)0;
-#pragma unroll
-    for (int q = 0; q < P; ++q) s += __shfl(mine, gbase + q, 64);
-    tot[a] = s;
-  }
-  if (on && tx == 0) {
+  gather_field<T, P>(field, g.K[0] + P - 1, g.K[1], g.K[2], sp & 1023, (sp >> 10) & 1023, sp >> 20, pt.x, pt.y, pt.z,
+                     fx * pt.w, fy * pt.w, fz * pt.w, t, grp * S::L, on, tot);
+  if (on && t == 0) {
     T* out = (src < n_ion) ? (ion_f + 3 * (int64_t)src) : (wc_f + 3 * ((int64_t)src - n_ion));
 #pragma unroll
     for (int a = 0; a < 3; ++a) out[a] = accumulate ? out[a] + tot[a] : tot[a];
