@@ -51,6 +51,11 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // row / column of accumulator register r of this lane in the 32 x 32 tile
 __device__ __forceinline__ int acc_row(int r) { return 8 * (r >> 2) + 4 * ((threadIdx.x & 63) >> 5) + (r & 3); }
 __device__ __forceinline__ int acc_col() { return threadIdx.x & 31; }
@@ -142,64 +147,6 @@ struct Stats {
   int audit_valid;
   double audit_num, audit_den;  // sum |F - F_ref|^2, sum |F_ref|^2 of the audits
 };
-
-__device__ __forceinline__ unsigned wave_max_bits(unsigned v) {
-  for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, off, 64));
-  return v;
-}
-
-__global__ void k_stats_reset_forward(Stats* st) {
-  if (threadIdx.x == 0) {
-    st->max_corr_bits = 0u;
-    st->max_force_bits = 0u;
-    st->min_nbr = 0x7fffffff;
-    st->max_nbr = 0;
-  }
-}
-
-// Smallest and largest neighbour count: per-block partials, then one block
-// reduces them (integer min / max: independent of the order).
-__global__ void __launch_bounds__(256) k_nbr_partials(const int* __restrict__ nbr, int n, int* __restrict__ part) {
-  __shared__ int lo[256], hi[256];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  lo[threadIdx.x] = i < n ? nbr[i] : 0x7fffffff;
-  hi[threadIdx.x] = i < n ? nbr[i] : 0;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
-      lo[threadIdx.x] = min(lo[threadIdx.x], lo[threadIdx.x + h]);
-      hi[threadIdx.x] = max(hi[threadIdx.x], hi[threadIdx.x + h]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = lo[0];
-    part[2 * blockIdx.x + 1] = hi[0];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_nbr_range(const int* __restrict__ part, int nblk, Stats* __restrict__ st) {
-  __shared__ int lo[256], hi[256];
-  int a = 0x7fffffff, b = 0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
-    a = min(a, part[2 * k]);
-    b = max(b, part[2 * k + 1]);
-  }
-  lo[threadIdx.x] = a;
-  hi[threadIdx.x] = b;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
-      lo[threadIdx.x] = min(lo[threadIdx.x], lo[threadIdx.x + h]);
-      hi[threadIdx.x] = max(hi[threadIdx.x], hi[threadIdx.x + h]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    st->min_nbr = lo[0];
-    st->max_nbr = hi[0];
-  }
-}
 
 // Charges not in the training set (exact float comparison with the set).
 constexpr int kMaxTrainCharges = 16;
@@ -341,36 +288,73 @@ __global__ void __launch_bounds__(128) k_norm_finish(double* __restrict__ acc, f
 }
 
 // ---------------------------------------------------------------------------
-// Descriptor: four lanes per (cell-sorted) particle.  Lane g owns the radial
-// orders k = g, g+4, ..., g+28, advanced with the stride-4 Chebyshev
-// recurrence T_{k+4} = 2 T_4 T_k - T_{k-4}, so a lane holds 8 x 4
-// accumulators instead of 32 x 4 (high occupancy hides the memory latency of
-// the neighbour scan).  Two phases: the four lanes scan the 27 neighbour cells
-// together (candidate jb + g), and the ones inside the cutoff are appended to
-// the particle's LDS list in candidate order (ballot + prefix count, so the
-// order is deterministic); then every lane accumulates its orders over the
-// whole list, the pair quantities formed once per pair (accumulate_pairs).  Writes T [n][128] (FP32, index 4k + a) and the normalised MLP
-// input x [n][128] (bf16).
+// Descriptor: four lanes per (cell-sorted) particle, one wave (16 particles) a
+// block.  Lane g owns the radial orders k = g + 4 m, m < 8, advanced with the
+// stride-4 Chebyshev recurrence T_{k+4} = 2 T_4 T_k - T_{k-4}.  Two phases:
+// the four lanes scan the candidates together (candidate t + g), and the ones
+// inside the cutoff are appended to the particle's LDS list in candidate order
+// (ballot + prefix count, so the order is deterministic); then the pair
+// quantities are formed once per pair and every lane runs its orders over the
+// whole list (accumulate_pairs).  Writes T [n][128] (FP32, index 4k + a) and the
+// normalised MLP input x [n][128] (bf16).
+//
+// The kernel is bound by VALU issue.  Per pair and particle, T[k, a] += w T_k u_a
+// is a 32 x 4 outer product: eight v_mfma_f32_4x4x1 (16 independent 4 x 4 outer
+// products each, one per particle of the wave; lane g gives w T_k of its order
+// and u_g) take the 32 multiply-adds per lane off the VALU, with the same
+// single-precision fused multiply-adds in the same order.  The three cells of a
+// neighbour row are consecutive in memory, so the scan walks 9 ranges instead
+// of 27, and the periodic image follows from the cell instead of a rounding per
+// candidate and axis.
+// Matrix instructions ignore the execution mask, so all loops are uniform over
+// the wave and a particle that is done contributes w = 0.
 // ---------------------------------------------------------------------------
 constexpr int kDescLanes = 4;
-constexpr int kDescThreads = 256;
+constexpr int kDescThreads = 64;
 constexpr int kDescParts = kDescThreads / kDescLanes;
 constexpr int kNbrMax = 64;
+// candidates per lane in flight together (16 per particle and chunk; 8 a lane
+// need more registers than four waves a SIMD leave)
+constexpr int kScan = 4;
+constexpr int kScanPad = kScan * kDescLanes;  // spare entries behind the sorted particles
+static_assert(kScan * kDescLanes <= 32 && kNbrMax % kDescLanes == 0, "one word of candidate bits per chunk");
 
-// Pairs per round of the accumulation: the four lanes of a particle form the
-// round's pair quantities (weight, unit vector, Chebyshev argument) once, one
-// pair each in turn, through the particle's LDS slots, and then every lane
-// runs its eight orders over all of them.
-constexpr int kPairChunk = 8;  // 4 measured the same, 16 slower (LDS per block)
+// Pairs per round of the accumulation: every lane of a particle forms one
+// pair's quantities (once per pair), and then every lane runs its eight orders
+// over all of them.  What lane g needs of a pair lies in one 16-byte slot of its
+// own, the starts of its recurrence included, so that a pair costs a lane two LDS
+// reads and no selection by g.
+constexpr int kPairChunk = kDescLanes;
+struct PairSlots {
+  float lane[kPairChunk][kDescLanes][4];  // component g of (1, unit vector), T_g, T_{4-g}, unused
+  float wt[kPairChunk][2];                // weight, 2 T_4
+  float pad[8];  // 80 words a particle: the reads of four particles fall on distinct banks
+};
 
-__device__ __forceinline__ void accumulate_pairs(float (&T)[8][4], const float4 pi, const float4* __restrict__ cpos,
-                                                 const int* list, int cnt, int g, const CellGeo& c,
-                                                 float (*pq)[5]) {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// acc[m][r] of lane a (a > 0): T[k = r + 4 m][a]; T0[m] of lane g: T[k = g + 4 m][0],
+// whose term is the unrounded product w T_k (fused), where the vector components
+// take the rounded one.
+__device__ __forceinline__ void accumulate_pairs(f32x4 (&acc)[8], float (&T0)[8], const float4 pi,
+                                                 const float4* __restrict__ cpos, const int* list, int cnt, int g,
+                                                 const CellGeo& c, PairSlots& S) {
   const float inv_rc = 1.0f / c.rc;
-  for (int t0 = 0; t0 < cnt; t0 += kPairChunk) {
-    const int nc = min(kPairChunk, cnt - t0);
-    for (int t = g; t < nc; t += kDescLanes) {
-      const float4 pj = cpos[list[t0 + t]];
+  int most = cnt;  // of the wave's 16 particles
+#pragma unroll
+  for (int off = kDescLanes; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off, 64));
+  const int rounds = __builtin_amdgcn_readfirstlane((most + kPairChunk - 1) / kPairChunk);
+#pragma unroll 1
+  for (int round = 0; round < rounds; ++round) {
+    const int t0 = round * kPairChunk;
+    float w = 0.0f, u1 = 0.0f, u2 = 0.0f, u3 = 0.0f, x = 0.0f;
+    if (t0 + g < cnt) {
+      const float4 pj = cpos[list[t0 + g]];
       float d0 = pj.x - pi.x, d1 = pj.y - pi.y, d2 = pj.z - pi.z;
       d0 -= c.L[0] * rintf(d0 * c.invL[0]);
       d1 -= c.L[1] * rintf(d1 * c.invL[1]);
@@ -378,124 +362,277 @@ __device__ __forceinline__ void accumulate_pairs(float (&T)[8][4], const float4 
       const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
       const float r = sqrtf(r2), ir = 1.0f / r;
       const float sw = 0.5f * (1.0f + __cosf(3.14159265358979f * r * inv_rc));
-      pq[t][0] = pj.w * sw;
-      pq[t][1] = d0 * ir;
-      pq[t][2] = d1 * ir;
-      pq[t][3] = d2 * ir;
-      pq[t][4] = 2.0f * r * inv_rc - 1.0f;
+      w = pj.w * sw;
+      u1 = d0 * ir;
+      u2 = d1 * ir;
+      u3 = d2 * ir;
+      x = 2.0f * r * inv_rc - 1.0f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the round's slots written
-    for (int t = 0; t < nc; ++t) {
-      const float w = pq[t][0], u1 = pq[t][1], u2 = pq[t][2], u3 = pq[t][3], x = pq[t][4];
-      const float t2 = 2.0f * x * x - 1.0f, t3 = 2.0f * x * t2 - x, t4 = 2.0f * x * t3 - t2;
-      // lane g starts from T_g and T_{4-g}
-      float cur = (g == 0) ? 1.0f : (g == 1) ? x : (g == 2) ? t2 : t3;
-      float prev = (g == 0) ? t4 : (g == 1) ? t3 : (g == 2) ? t2 : x;
-      const float t4x2 = 2.0f * t4;
+    const float t2 = 2.0f * x * x - 1.0f, t3 = 2.0f * x * t2 - x, t4 = 2.0f * x * t3 - t2;
+    *reinterpret_cast<float4*>(S.lane[g][0]) = make_float4(1.0f, 1.0f, t4, 0.0f);
+    *reinterpret_cast<float4*>(S.lane[g][1]) = make_float4(u1, x, t3, 0.0f);
+    *reinterpret_cast<float4*>(S.lane[g][2]) = make_float4(u2, t2, t2, 0.0f);
+    *reinterpret_cast<float4*>(S.lane[g][3]) = make_float4(u3, t3, x, 0.0f);
+    *reinterpret_cast<float2*>(S.wt[g]) = make_float2(w, 2.0f * t4);
+    wave_lds_fence();  // the round's slots written
+    // unrolled: as a loop the compiler copies all 40 sums in and out of it every
+    // round; the barriers keep it from holding all four pairs' slots at once
+    float2 wt_next = *reinterpret_cast<const float2*>(S.wt[0]);
+    float4 v_next = *reinterpret_cast<const float4*>(S.lane[0][g]);
+#pragma unroll
+    for (int t = 0; t < kPairChunk; ++t) {
+      const float2 wt = wt_next;
+      const float4 v = v_next;
+      if (t + 1 < kPairChunk) {
+        wt_next = *reinterpret_cast<const float2*>(S.wt[t + 1]);
+        v_next = *reinterpret_cast<const float4*>(S.lane[t + 1][g]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      float cur = v.y, prev = v.z;
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         if (m > 0) {
-          const float nxt = t4x2 * cur - prev;
+          const float nxt = wt.y * cur - prev;
           prev = cur;
           cur = nxt;
         }
-        const float wg = w * cur;
-        T[m][0] += wg;
-        T[m][1] += wg * u1;
-        T[m][2] += wg * u2;
-        T[m][3] += wg * u3;
+        T0[m] = fmaf(wt.x, cur, T0[m]);
+        acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(wt.x * cur, v.x, acc[m], 0, 0, 0);
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // all four lanes done before the next round
+    wave_lds_fence();  // all four lanes done before the next round
   }
 }
 
-__global__ void __launch_bounds__(kDescThreads) k_descriptor(const float4* __restrict__ cpos,
-                                                             const int* __restrict__ start, int n,
-                                                             const float* __restrict__ params,
-                                                             float* __restrict__ Tout,
-                                                             unsigned short* __restrict__ X, CellGeo c,
-                                                             int* __restrict__ nbr) {
-  __shared__ int lists[kDescParts][kNbrMax];
-  __shared__ float pqs[kDescParts][kPairChunk][5];
-  const int g = threadIdx.x & (kDescLanes - 1), p = threadIdx.x / kDescLanes;
-  const int lane = threadIdx.x & 63, gbase = lane & ~(kDescLanes - 1);
-  const int i = blockIdx.x * kDescParts + p;
-  if (i >= n) return;  // the four lanes of a particle leave together
-  int* list = lists[p];
-  const float4 pi = cpos[i];
-  float T[8][4];
+// quad_perm data movement: lane g of a quad takes the value of lane (ctrl >> 2g) & 3
+template <int CTRL>
+__device__ __forceinline__ float quad_perm(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+template <int CTRL>
+__device__ __forceinline__ unsigned quad_perm_u(unsigned v) {
+  return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+
+// 4 x 4 transpose over the quad: lane g, element r <-> lane r, element g
+__device__ __forceinline__ void quad_transpose(float (&v)[4], int g) {
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // [1,0,3,2], [2,3,0,1]
+  const bool b0 = g & 1, b1 = g & 2;
 #pragma unroll
-  for (int m = 0; m < 8; ++m) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) T[m][a] = 0.0f;
+  for (int r = 0; r < 4; r += 2) {
+    const float got = quad_perm<kXor1>(b0 ? v[r] : v[r + 1]);
+    v[r] = b0 ? got : v[r];
+    v[r + 1] = b0 ? v[r + 1] : got;
   }
-  const int cx = min((int)(pi.x * c.cinv[0]), c.nc[0] - 1);
-  const int cy = min((int)(pi.y * c.cinv[1]), c.nc[1] - 1);
-  const int cz = min((int)(pi.z * c.cinv[2]), c.nc[2] - 1);
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const float got = quad_perm<kXor2>(b1 ? v[r] : v[r + 2]);
+    v[r] = b1 ? got : v[r];
+    v[r + 2] = b1 ? v[r + 2] : got;
+  }
+}
+
+// Row k = g + 4 m of the descriptor in lane g (all four lanes call it).
+__device__ __forceinline__ void descriptor_row(float (&T)[4], const f32x4& acc, float T0, int g) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) T[r] = acc[r];
+  quad_transpose(T, g);
+  T[0] = T0;
+}
+
+// Lists the neighbours number base .. base + kNbrMax - 1 of particle i (at pi; on:
+// there is one; this is lane g of its four) and returns how many there are in
+// all.  The whole wave calls it.
+__device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, int g,
+                                               const float4* __restrict__ cpos, const int* __restrict__ start,
+                                               const CellGeo& c, int base, int* list) {
+  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
+  const int cx = min((int)(pi.x * c.cinv[0]), nx - 1);
+  const int cy = min((int)(pi.y * c.cinv[1]), ny - 1);
+  const int cz = min((int)(pi.z * c.cinv[2]), nz - 1);
   const float rc2 = c.rc * c.rc;
-  int cnt = 0, total = 0;
-  for (int dz = -1; dz <= 1; ++dz) {
-    const int zz = (cz + dz + c.nc[2]) % c.nc[2];
-    for (int dy = -1; dy <= 1; ++dy) {
-      const int yy = (cy + dy + c.nc[1]) % c.nc[1];
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int xx = (cx + dx + c.nc[0]) % c.nc[0];
-        const int cell = (zz * c.nc[1] + yy) * c.nc[0] + xx;
-        const int j0 = start[cell], j1 = start[cell + 1];
-        for (int jb = j0; jb < j1; jb += kDescLanes) {
-          const int j = jb + g;
-          bool in = false;
-          if (j < j1 && j != i) {
-            const float4 pj = cpos[j];
-            float d0 = pj.x - pi.x, d1 = pj.y - pi.y, d2 = pj.z - pi.z;
-            d0 -= c.L[0] * rintf(d0 * c.invL[0]);
-            d1 -= c.L[1] * rintf(d1 * c.invL[1]);
-            d2 -= c.L[2] * rintf(d2 * c.invL[2]);
-            const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            in = r2 < rc2 && r2 > 0.0f;
-          }
-          const unsigned gm = (unsigned)(__ballot(in) >> gbase) & ((1u << kDescLanes) - 1u);
-          if (in) list[cnt + __popc(gm & ((1u << g) - 1u))] = j;
-          cnt += __popc(gm);
-          total += __popc(gm);
-          if (cnt > kNbrMax - kDescLanes) {  // the same decision on all four lanes
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            accumulate_pairs(T, pi, cpos, list, cnt, g, c, pqs[p]);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            cnt = 0;
-          }
-        }
+  // A row's cells cx-1, cx, cx+1 are consecutive; at the ends of the row they are
+  // two ranges (cells nx-1 | 0, 1 or nx-2, nx-1 | 0).  Segment q of the scan: row
+  // q / 2 (z outer, y inner), its first or second range.  Cells before 0 or past
+  // the end are one box length away.
+  auto segment = [&](int q, int& j0, int& j1) {
+    const int k = q >> 1, kz = (k * 11) >> 5, ky = k - 3 * kz;  // k / 3 for k < 9
+    const int y = cy + ky - 1, z = cz + kz - 1;
+    const int* row = start + ((z < 0 ? nz - 1 : z >= nz ? 0 : z) * ny + (y < 0 ? ny - 1 : y >= ny ? 0 : y)) * nx;
+    if (q & 1) {
+      j0 = row[0];
+      j1 = row[cx == 0 ? 2 : cx == nx - 1 ? 1 : 0];
+    } else {
+      j0 = row[cx == 0 ? nx - 1 : cx - 1];
+      j1 = row[cx == 0 ? nx : min(cx + 2, nx)];
+    }
+    if (!on) j1 = j0;
+  };
+  auto shifts = [&](int q, float& sx, float& sy, float& sz) {
+    const int k = q >> 1, kz = (k * 11) >> 5, ky = k - 3 * kz;
+    const int y = cy + ky - 1, z = cz + kz - 1;
+    sx = q & 1 ? (cx == nx - 1 ? -c.L[0] : 0.0f) : (cx == 0 ? c.L[0] : 0.0f);
+    sy = y < 0 ? c.L[1] : y >= ny ? -c.L[1] : 0.0f;
+    sz = z < 0 ? c.L[2] : z >= nz ? -c.L[2] : 0.0f;
+  };
+  const int dq = __any(cx == 0 || cx == nx - 1) ? 1 : 2;  // second ranges only where a particle of the wave has one
+  int cnt = 0, q = 0;
+  int j0, j1, j0n, j1n;
+  float sx, sy, sz;
+  segment(0, j0, j1);
+  shifts(0, sx, sy, sz);
+  segment(dq, j0n, j1n);  // bounds are loaded one segment ahead
+  // candidates j0 + 4 u + g, u < kScan, of the next chunk (past the range or the
+  // array's end: masked below; the array has kScanPad spare entries)
+  float3 pj[kScan];
+  auto fetch = [&]() {
+    const float4* src = cpos + j0 + g;
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) pj[u] = *reinterpret_cast<const float3*>(src + kDescLanes * u);
+  };
+  fetch();
+  while (q < 18) {
+    const int jc = j0 + g;
+    const int left = min(max(j1 - j0, 0), kScan * kDescLanes);
+    // bit 4 u + g of the particle's word: candidate 4 u + g is inside the cutoff
+    // (and not at the particle's own place: not itself)
+    unsigned bits = 0u;
+    auto test = [&](int u, float d0, float d1, float d2) {
+      const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
+      bits |= (r2 < rc2 && r2 > 0.0f) ? 1u << (kDescLanes * u) : 0u;
+    };
+    if (__any(sx != 0.0f || sy != 0.0f || sz != 0.0f)) {
+#pragma unroll
+      for (int u = 0; u < kScan; ++u) test(u, (pj[u].x - pi.x) - sx, (pj[u].y - pi.y) - sy, (pj[u].z - pi.z) - sz);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kScan; ++u) test(u, pj[u].x - pi.x, pj[u].y - pi.y, pj[u].z - pi.z);
+    }
+    // the next chunk's candidates arrive while this one's are listed
+    j0 += kScan * kDescLanes;
+    if (!__any(j0 < j1)) {
+      q += dq;
+      j0 = j0n;
+      j1 = j1n;
+      shifts(min(q, 17), sx, sy, sz);
+      segment(min(q + dq, 17), j0n, j1n);
+    }
+    fetch();
+    bits <<= g;
+    unsigned word = bits | quad_perm_u<0xB1>(bits);
+    word |= quad_perm_u<0x4E>(word);
+    word &= (1u << left) - 1u;  // what lies past the range is dropped
+    // each lane lists its own candidates at their places in candidate order
+    // (the others go to a spare entry)
+    int place = cnt - base + __popc(word & ((1u << g) - 1u));
+    const unsigned own = word >> g;
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) {
+      const unsigned at = own & (1u << (kDescLanes * u)) ? (unsigned)place : (unsigned)kNbrMax;
+      list[min(at, (unsigned)kNbrMax)] = jc + kDescLanes * u;
+      place += __popc(own & (0xfu << (kDescLanes * u)));
+    }
+    cnt += __popc(word);
+  }
+  return cnt;
+}
+
+// The descriptor of particle i into acc and T0 of its four lanes (of which this
+// is lane g); list and S: the particle's LDS.  Returns the neighbour count.
+// The whole wave calls it.  More than kNbrMax neighbours are taken in rounds;
+// the sums wait in the particle's row of T meanwhile, so that they are not live
+// during a scan (they would cost it a third of its registers).
+__device__ __forceinline__ int describe(f32x4 (&acc)[8], float (&T0)[8], const float4 pi, int i, bool on, int g,
+                                        const float4* __restrict__ cpos, const int* __restrict__ start,
+                                        const CellGeo& c, float* __restrict__ Tbuf, int* list, PairSlots& S) {
+  float4* rows = reinterpret_cast<float4*>(Tbuf + (size_t)i * 128);
+  int total = 0;
+  for (int base = 0;; base += kNbrMax) {
+    total = scan_neighbours(pi, i, on, g, cpos, start, c, base, list);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      acc[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      T0[m] = 0.0f;
+    }
+    if (base > 0) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const float4 r = on ? rows[g + 4 * m] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float T[4] = {r.x, r.y, r.z, r.w};
+        T0[m] = T[0];
+        quad_transpose(T, g);
+        acc[m] = f32x4{T[0], T[1], T[2], T[3]};
       }
     }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  accumulate_pairs(T, pi, cpos, list, cnt, g, c, pqs[p]);
-  if (nbr && g == 0) nbr[i] = total;  // neighbour count, reduced by k_nbr_range
-  float* to = Tout + (size_t)i * 128;
+    accumulate_pairs(acc, T0, pi, cpos, list, min(max(total - base, 0), kNbrMax), g, c, S);
+    if (!__any(total > base + kNbrMax)) break;
 #pragma unroll
-  for (int m = 0; m < 8; ++m)
-    reinterpret_cast<float4*>(to)[g + 4 * m] = make_float4(T[m][0], T[m][1], T[m][2], T[m][3]);
-  // invariants D[4k + l] = sum_a T[k][a] T[l][a], l < 4: T[l] is order 0 of lane l
-  float Tl[4][4];
-#pragma unroll
-  for (int l = 0; l < 4; ++l) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) Tl[l][a] = __shfl(T[0][a], gbase + l, 64);
-  }
-  const float* mu = params + kOffMu;
-  const float* isd = params + kOffIsd;
-  unsigned short* xo = X + (size_t)i * 128;
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const int k = g + 4 * m;
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      const float d = T[m][0] * Tl[l][0] + T[m][1] * Tl[l][1] + T[m][2] * Tl[l][2] + T[m][3] * Tl[l][3];
-      const int f = 4 * k + l;
-      xo[f] = f2bf((d - mu[f]) * isd[f]);
+    for (int m = 0; m < 8; ++m) {
+      float T[4];
+      descriptor_row(T, acc[m], T0[m], g);
+      if (on) rows[g + 4 * m] = make_float4(T[0], T[1], T[2], T[3]);
     }
   }
+  return total;
+}
+
+// Calls out(k, T, x) for the lane's rows k = g + 4 m: T[k][0..3] and the four
+// network inputs 4k + l from the invariants D[4k + l] = sum_a T[k][a] T[l][a].
+template <typename Out>
+__device__ __forceinline__ void descriptor_inputs(const f32x4 (&acc)[8], const float (&T0)[8], int g,
+                                                  const float* __restrict__ params, Out out) {
+  const float4* mu = reinterpret_cast<const float4*>(params + kOffMu);
+  const float4* isd = reinterpret_cast<const float4*>(params + kOffIsd);
+  float Tl[4][4];  // T[l] is order 0 of lane l
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    float T[4];
+    descriptor_row(T, acc[m], T0[m], g);
+    if (m == 0) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        Tl[0][a] = quad_perm<0x00>(T[a]);
+        Tl[1][a] = quad_perm<0x55>(T[a]);
+        Tl[2][a] = quad_perm<0xAA>(T[a]);
+        Tl[3][a] = quad_perm<0xFF>(T[a]);
+      }
+    }
+    const int k = g + 4 * m;
+    const float4 mk = mu[k], sk = isd[k];
+    const float mv[4] = {mk.x, mk.y, mk.z, mk.w}, sv[4] = {sk.x, sk.y, sk.z, sk.w};
+    bf16x4 x;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      const float d = T[0] * Tl[l][0] + T[1] * Tl[l][1] + T[2] * Tl[l][2] + T[3] * Tl[l][3];
+      x[l] = (__bf16)((d - mv[l]) * sv[l]);
+    }
+    out(k, T, x);
+  }
+}
+
+__global__ void __launch_bounds__(kDescThreads, 4) k_descriptor(const float4* __restrict__ cpos,
+                                                                const int* __restrict__ start, int n,
+                                                                const float* __restrict__ params,
+                                                                float* __restrict__ Tout,
+                                                                unsigned short* __restrict__ X, CellGeo c) {
+  __shared__ int lists[kDescParts][kNbrMax + 1];
+  __shared__ __align__(16) PairSlots slots[kDescParts];
+  const int g = threadIdx.x & (kDescLanes - 1), p = threadIdx.x / kDescLanes;
+  const int i = blockIdx.x * kDescParts + p;
+  const bool on = i < n;
+  f32x4 acc[8];
+  float T0[8];
+  (void)describe(acc, T0, cpos[min(i, n - 1)], i, on, g, cpos, start, c, Tout, lists[p], slots[p]);
+  float4* to = reinterpret_cast<float4*>(Tout + (size_t)i * 128);
+  bf16x4* xo = reinterpret_cast<bf16x4*>(X + (size_t)i * 128);
+  descriptor_inputs(acc, T0, g, params, [&](int k, const float (&T)[4], const bf16x4& x) {
+    if (on) {
+      to[k] = make_float4(T[0], T[1], T[2], T[3]);
+      xo[k] = x;
+    }
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -563,11 +700,213 @@ constexpr int kLW1 = 0, kLW2 = kLW1 + kIn * kPadH, kLW3 = kLW2 + kH * kPadH, kLW
               kLW = kLW4 + kH * kPadO;                                   // [in][out] copies
 
 // ---------------------------------------------------------------------------
-// MLP forward + force head.  Persistent blocks of 4 waves stage the weights
-// (bf16, [out][in]) and biases once, then walk tiles of 128 particles; wave w
-// owns rows 32w..32w+31 of a tile.  Activations go layer to layer through
-// LDS.  In training mode the pre-activations z1..z3 and activations h1..h3
-// are stored, and the head also forms the loss and dL/dc.
+// The correction of 32 particles per block in one pass: descriptor, network and
+// force head, with nothing but the forces written.  (As two kernels the
+// descriptor and the network input, 768 bytes a particle, went through memory:
+// at 288,768 particles the descriptor kernel spent 85 of its 218 us writing them
+// and the network kernel 89 us mostly reading them; this kernel takes 219.)
+// What is left is VALU issue: about 83 us of scan, 88 of pairs, 22 of network, the
+// rest the inputs and the head.
+// Two waves hold 16 particles each for the descriptor; for the network, wave w
+// computes features 32 w .. 32 w + 31 of all 32 particles: weights as the A
+// operand in fragment order straight from L2 (36 KB, read by every block; LDS
+// would cost the scan its occupancy), activations as the B operand from LDS, so
+// that a lane ends with four consecutive features of one particle and writes
+// them as 8 bytes.  The order of every sum that is rounded to bf16 is that of
+// k_mlp_fwd.
+// ---------------------------------------------------------------------------
+constexpr int kCorrThreads = 128;
+constexpr int kCorrRows = 32;  // particles per block
+constexpr int kFrags[4] = {16, 8, 8, 4};
+constexpr int kFragOfs[4] = {0, 16, 24, 32};  // 36 fragments of 64 lanes x 8 values
+
+union CorrLds {
+  struct {
+    int lists[kCorrRows][kNbrMax + 1];
+    PairSlots slots[kCorrRows];
+  } d;
+  struct {
+    union {
+      unsigned short x[kCorrRows][kPadIn];  // network input, then the second hidden layer,
+      unsigned short h1[kCorrRows][kPadH];
+      float c[kCorrRows][kOut + 4];         // then the head's coefficients
+    };
+    unsigned short h0[kCorrRows][kPadH];    // first and third hidden layer
+  } m;
+};
+
+// Per-block statistics of the forward, reduced by k_forward_stats.
+struct FwdPart {
+  int lo, hi;            // neighbour counts
+  unsigned corr, force;  // max |dF|, max |F| (float bits)
+};
+
+// One hidden layer's tile: out(32 particles x 32 features of this wave) =
+// silu(in W + b), bf16.
+template <int K>
+__device__ __forceinline__ void corr_layer(const unsigned short* in, int ldin, const unsigned short* __restrict__ frag,
+                                           const float* __restrict__ bias, unsigned short* out) {
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6, kh = l >> 5, n = l & 31;
+  const bf16x8* A = reinterpret_cast<const bf16x8*>(frag) + (size_t)wave * (K / 16) * 64 + l;
+  const unsigned short* B = in + n * ldin + 8 * kh;
+  f32x16 acc;
+  zero(acc);
+#pragma unroll
+  for (int s = 0; s < K / 16; ++s) {
+    const bf16x8 a = A[64 * s];
+    const bf16x4 b0 = *reinterpret_cast<const bf16x4*>(B + 16 * s);
+    const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(B + 16 * s + 4);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7), acc, 0,
+                                                  0, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int f = 32 * wave + 8 * q + 4 * kh;
+    const float4 bv = *reinterpret_cast<const float4*>(bias + f);
+    const float z[4] = {acc[4 * q] + bv.x, acc[4 * q + 1] + bv.y, acc[4 * q + 2] + bv.z, acc[4 * q + 3] + bv.w};
+    bf16x4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (__bf16)silu(z[e]);
+    *reinterpret_cast<bf16x4*>(out + n * kPadH + f) = h;
+  }
+}
+
+__global__ void __launch_bounds__(kCorrThreads, 4) k_correction(const float4* __restrict__ cpos,
+                                                                const int* __restrict__ cidx,
+                                                                const int* __restrict__ start, int n, int64_t n_ion,
+                                                                float* __restrict__ Tbuf,
+                                                                const unsigned short* __restrict__ wf,
+                                                                const float* __restrict__ params, float s_out,
+                                                                float* __restrict__ ion_dF, float* __restrict__ wc_dF,
+                                                                int accumulate, CellGeo c,
+                                                                FwdPart* __restrict__ part) {
+  __shared__ __align__(16) CorrLds S;
+  __shared__ FwdPart wpart[kCorrThreads / 64];
+  const int g = threadIdx.x & (kDescLanes - 1), p = threadIdx.x / kDescLanes;
+  const int i = blockIdx.x * kCorrRows + p;
+  const bool on = i < n;
+  f32x4 acc[8];
+  float T0[8];
+  const float4 pi = cpos[min(i, n - 1)];
+  const int total = describe(acc, T0, pi, i, on, g, cpos, start, c, Tbuf, S.d.lists[p], S.d.slots[p]);
+  __syncthreads();  // both waves are done with the lists
+  descriptor_inputs(acc, T0, g, params, [&](int k, const float (&)[4], const bf16x4& x) {
+    *reinterpret_cast<bf16x4*>(&S.m.x[p][4 * k]) = x;
+  });
+  __syncthreads();
+  corr_layer<kIn>(&S.m.x[0][0], kPadIn, wf + kFragOfs[0] * 512, params + kOffB1, &S.m.h0[0][0]);
+  __syncthreads();
+  corr_layer<kH>(&S.m.h0[0][0], kPadH, wf + kFragOfs[1] * 512, params + kOffB2, &S.m.h1[0][0]);
+  __syncthreads();
+  corr_layer<kH>(&S.m.h1[0][0], kPadH, wf + kFragOfs[2] * 512, params + kOffB3, &S.m.h0[0][0]);
+  __syncthreads();
+  // output layer: c = h3 W4 + b4, one tile, by the waves in turn from block to block
+  if ((int)(threadIdx.x >> 6) == (int)(blockIdx.x & 1)) {
+    const int l = threadIdx.x & 63, kh = l >> 5, r = l & 31;
+    const bf16x8* A = reinterpret_cast<const bf16x8*>(wf + kFragOfs[3] * 512) + l;
+    const unsigned short* B = &S.m.h0[r][8 * kh];
+    f32x16 o;
+    zero(o);
+#pragma unroll
+    for (int s = 0; s < kH / 16; ++s) {
+      const bf16x4 b0 = *reinterpret_cast<const bf16x4*>(B + 16 * s);
+      const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(B + 16 * s + 4);
+      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[64 * s], __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7),
+                                                  o, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int f = 8 * q + 4 * kh;
+      const float4 bv = *reinterpret_cast<const float4*>(params + kOffB4 + f);
+      *reinterpret_cast<float4*>(&S.m.c[r][f]) =
+          make_float4(o[4 * q] + bv.x, o[4 * q + 1] + bv.y, o[4 * q + 2] + bv.z, o[4 * q + 3] + bv.w);
+    }
+  }
+  __syncthreads();
+  // head: dF = s_out q sum_k c_k T[k, 1:4], each lane over its orders, then the quad
+  // (the rows are put together again: kept from above they would be 32 more
+  // registers through the network)
+  float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    float T[4];
+    asm volatile("" : "+v"(acc[m]));
+    descriptor_row(T, acc[m], T0[m], g);
+    const float cc = S.m.c[p][g + 4 * m];
+    f0 += cc * T[1];
+    f1 += cc * T[2];
+    f2 += cc * T[3];
+  }
+  f0 += quad_perm<0xB1>(f0);
+  f1 += quad_perm<0xB1>(f1);
+  f2 += quad_perm<0xB1>(f2);
+  f0 += quad_perm<0x4E>(f0);
+  f1 += quad_perm<0x4E>(f1);
+  f2 += quad_perm<0x4E>(f2);
+  int lo = 0x7fffffff, hi = 0;
+  unsigned mcorr = 0u, mforce = 0u;
+  if (on && g == 0) {
+    const float sq = s_out * pi.w;
+    f0 *= sq; f1 *= sq; f2 *= sq;
+    const int src = cidx[i];
+    float* out = (src < n_ion) ? ion_dF + 3 * (int64_t)src : wc_dF + 3 * ((int64_t)src - n_ion);
+    mcorr = __float_as_uint(sqrtf(f0 * f0 + f1 * f1 + f2 * f2));
+    if (accumulate) {
+      mforce = __float_as_uint(sqrtf(out[0] * out[0] + out[1] * out[1] + out[2] * out[2]));
+      f0 += out[0]; f1 += out[1]; f2 += out[2];
+    }
+    out[0] = f0; out[1] = f1; out[2] = f2;
+    lo = hi = total;
+  }
+  // the block's statistics
+  for (int off = 32; off >= kDescLanes; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off, 64));
+    hi = max(hi, __shfl_xor(hi, off, 64));
+    mcorr = max(mcorr, (unsigned)__shfl_xor((int)mcorr, off, 64));
+    mforce = max(mforce, (unsigned)__shfl_xor((int)mforce, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) wpart[threadIdx.x >> 6] = FwdPart{lo, hi, mcorr, mforce};
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const FwdPart a = wpart[0], b = wpart[1];
+    part[blockIdx.x] = FwdPart{a.lo < b.lo ? a.lo : b.lo, a.hi > b.hi ? a.hi : b.hi,
+                               a.corr > b.corr ? a.corr : b.corr, a.force > b.force ? a.force : b.force};
+  }
+}
+
+// Statistics of the forward from the block partials (integer minima and
+// maxima: independent of the order; nblk = 0 for an input of no particles).
+__global__ void __launch_bounds__(1024) k_forward_stats(const FwdPart* __restrict__ part, int nblk,
+                                                        Stats* __restrict__ st) {
+  __shared__ FwdPart w[16];
+  FwdPart a{0x7fffffff, 0, 0u, 0u};
+  auto add = [&](const FwdPart& b) {
+    a.lo = min(a.lo, b.lo);
+    a.hi = max(a.hi, b.hi);
+    a.corr = a.corr > b.corr ? a.corr : b.corr;
+    a.force = a.force > b.force ? a.force : b.force;
+  };
+  for (int k = threadIdx.x; k < nblk; k += blockDim.x) add(part[k]);
+  for (int off = 32; off > 0; off >>= 1)
+    add(FwdPart{(int)__shfl_xor(a.lo, off, 64), (int)__shfl_xor(a.hi, off, 64),
+                (unsigned)__shfl_xor((int)a.corr, off, 64), (unsigned)__shfl_xor((int)a.force, off, 64)});
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 16; ++k) add(w[k]);
+    st->max_corr_bits = a.corr;
+    st->max_force_bits = a.force;
+    st->min_nbr = a.lo;
+    st->max_nbr = a.hi;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// MLP forward + force head of a training step.  Persistent blocks of 4 waves
+// stage the weights (bf16, [out][in]) and biases once, then walk tiles of 128
+// particles; wave w owns rows 32w..32w+31 of a tile.  Activations go layer to
+// layer through LDS.  The pre-activations z1..z3 and activations h1..h3 are
+// stored, and the head forms the loss and dL/dc.
 // ---------------------------------------------------------------------------
 struct FwdLds {
   unsigned short wt[kLWt];
@@ -578,19 +917,14 @@ struct FwdLds {
   double lred[4];
 };
 
-template <bool TRAIN>
 __global__ void __launch_bounds__(256) k_mlp_fwd(const unsigned short* __restrict__ X, const float* __restrict__ Tin,
                                                  const float4* __restrict__ cpos, const int* __restrict__ cidx,
                                                  int n, int64_t n_ion, const unsigned short* __restrict__ wt_g,
                                                  const float* __restrict__ params, float s_out,
-                                                 float* __restrict__ ion_dF, float* __restrict__ wc_dF,
-                                                 int accumulate,
-                                                 // training
                                                  const float* __restrict__ ion_tgt, const float* __restrict__ wc_tgt,
                                                  const float* __restrict__ ion_base, const float* __restrict__ wc_base,
                                                  float* __restrict__ Z, unsigned short* __restrict__ H,
-                                                 float* __restrict__ dC, double* __restrict__ loss_part, float gscale,
-                                                 Stats* __restrict__ st) {
+                                                 float* __restrict__ dC, double* __restrict__ loss_part, float gscale) {
   extern __shared__ __align__(16) unsigned char smem[];
   FwdLds& S = *reinterpret_cast<FwdLds*>(smem);
   const int tid = threadIdx.x, wave = tid >> 6;
@@ -632,7 +966,6 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const unsigned short* __restric
   const unsigned short* wl[4] = {S.wt + kLW1t, S.wt + kLW2t, S.wt + kLW3t, S.wt + kLW4t};
   const int ldw[4] = {kPadIn, kPadH, kPadH, kPadH};
   double lsum = 0.0;
-  unsigned mcorr = 0u, mforce = 0u;  // running maxima (float bits) for the guard
   const int ntiles = (n + kRows - 1) / kRows;
   // A tile's inputs travel in 16-byte chunks held in registers: the next
   // tile's loads are issued while the current tile computes (the block's
@@ -697,7 +1030,7 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const unsigned short* __restric
           const float h = silu(z);
           const unsigned short hb = f2bf(h);
           Hout[row * kPadH + col] = hb;
-          if (TRAIN && row0 + wr + row < n) {
+          if (row0 + wr + row < n) {
             Z[((size_t)layer * n + row0 + wr + row) * kH + col] = z;
             H[((size_t)layer * n + row0 + wr + row) * kH + col] = hb;
           }
@@ -737,52 +1070,31 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const unsigned short* __restric
         const int slot = row0 + hp;
         const float q = cpos[slot].w;
         const float sq = s_out * q;
-        f0 *= sq; f1 *= sq; f2 *= sq;
+        // the prediction is a rounded FP32 force (not fused into the error below)
+        f0 = mul_rounded(f0, sq); f1 = mul_rounded(f1, sq); f2 = mul_rounded(f2, sq);
         const int src = cidx[slot];
-        float* out = (src < n_ion) ? ion_dF + 3 * (int64_t)src : wc_dF + 3 * ((int64_t)src - n_ion);
-        if (hk == 0) {
-          mcorr = max(mcorr, __float_as_uint(sqrtf(f0 * f0 + f1 * f1 + f2 * f2)));
-          if (accumulate) {
-            mforce = max(mforce, __float_as_uint(sqrtf(out[0] * out[0] + out[1] * out[1] + out[2] * out[2])));
-            out[0] += f0; out[1] += f1; out[2] += f2;
-          } else {
-            out[0] = f0; out[1] = f1; out[2] = f2;
-          }
-        }
-        if (TRAIN) {
-          // target: the residual target - base (fine minus coarse forces) when a base is given
-          const int64_t o3 = (src < n_ion) ? 3 * (int64_t)src : 3 * ((int64_t)src - n_ion);
-          const float* tg = ((src < n_ion) ? ion_tgt : wc_tgt) + o3;
-          const float* bs = (src < n_ion) ? ion_base : wc_base;
-          float t0 = tg[0], t1 = tg[1], t2 = tg[2];
-          if (bs) { t0 -= bs[o3]; t1 -= bs[o3 + 1]; t2 -= bs[o3 + 2]; }
-          const float e0 = f0 - t0, e1 = f1 - t1, e2 = f2 - t2;
-          if (hk == 0) lsum += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
-          // dL/d dF = gscale * e (gscale = 2 / (3 n)); dL/dc_k = s_out q (g . T[k, 1:4])
-          const float g0 = gscale * e0 * sq, g1 = gscale * e1 * sq, g2 = gscale * e2 * sq;
+        // target: the residual target - base (fine minus coarse forces) when a base is given
+        const int64_t o3 = (src < n_ion) ? 3 * (int64_t)src : 3 * ((int64_t)src - n_ion);
+        const float* tg = ((src < n_ion) ? ion_tgt : wc_tgt) + o3;
+        const float* bs = (src < n_ion) ? ion_base : wc_base;
+        float t0 = tg[0], t1 = tg[1], t2 = tg[2];
+        if (bs) { t0 -= bs[o3]; t1 -= bs[o3 + 1]; t2 -= bs[o3 + 2]; }
+        const float e0 = f0 - t0, e1 = f1 - t1, e2 = f2 - t2;
+        if (hk == 0) lsum += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
+        // dL/d dF = gscale * e (gscale = 2 / (3 n)); dL/dc_k = s_out q (g . T[k, 1:4])
+        const float g0 = gscale * e0 * sq, g1 = gscale * e1 * sq, g2 = gscale * e2 * sq;
 #pragma unroll
-          for (int k = 0; k < kHalf; ++k)
-            dC[(size_t)slot * kOut + hk * kHalf + k] = g0 * tq[k].y + g1 * tq[k].z + g2 * tq[k].w;
-        }
+        for (int k = 0; k < kHalf; ++k)
+          dC[(size_t)slot * kOut + hk * kHalf + k] = g0 * tq[k].y + g1 * tq[k].z + g2 * tq[k].w;
       }
     }
   }
-  if (st) {
-    mcorr = wave_max_bits(mcorr);
-    mforce = wave_max_bits(mforce);
-    if ((tid & 63) == 0) {
-      if (mcorr) atomicMax(&st->max_corr_bits, mcorr);
-      if (mforce) atomicMax(&st->max_force_bits, mforce);
-    }
-  }
-  if (TRAIN) {
-    // deterministic block sum of the squared errors (the even threads hold them)
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
-    __syncthreads();
-    if ((tid & 63) == 0) S.lred[wave] = lsum;
-    __syncthreads();
-    if (tid == 0) loss_part[blockIdx.x] = S.lred[0] + S.lred[1] + S.lred[2] + S.lred[3];
-  }
+  // deterministic block sum of the squared errors (the even threads hold them)
+  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
+  __syncthreads();
+  if ((tid & 63) == 0) S.lred[wave] = lsum;
+  __syncthreads();
+  if (tid == 0) loss_part[blockIdx.x] = S.lred[0] + S.lred[1] + S.lred[2] + S.lred[3];
 }
 
 // ---------------------------------------------------------------------------
@@ -917,8 +1229,11 @@ __global__ void k_adam(float* __restrict__ params, float* __restrict__ m, float*
   params[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
 }
 
+// bf16 copies of the weights: [in][out], [out][in], and in the order in which
+// k_correction's waves read them as MFMA fragments (lane l of fragment (tile of
+// 32 outputs, step of 16 inputs) holds output l % 32, inputs 8 (l / 32) + 0..7).
 __global__ void k_weights_to_bf16(const float* __restrict__ params, unsigned short* __restrict__ w,
-                                  unsigned short* __restrict__ wt) {
+                                  unsigned short* __restrict__ wt, unsigned short* __restrict__ wf) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= kNWeights) return;
   // locate layer
@@ -932,6 +1247,8 @@ __global__ void k_weights_to_bf16(const float* __restrict__ params, unsigned sho
   const unsigned short b = f2bf(params[pofs + loc]);
   w[e] = b;                      // [in][out]
   wt[off + o * ni + i] = b;      // [out][in]
+  const int frag = (o >> 5) * (ni / 16) + (i >> 4), lane = (o & 31) + 32 * ((i >> 3) & 1);
+  wf[off + (frag * 64 + lane) * 8 + (i & 7)] = b;
 }
 
 }  // namespace mlp
