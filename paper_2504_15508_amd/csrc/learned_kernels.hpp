@@ -28,7 +28,7 @@ constexpr int kOffMu = kNTrain, kOffIsd = kOffMu + kIn;
 constexpr int kNParams = kOffIsd + kIn;               // packed total
 constexpr int kNWeights = kIn * kH + 2 * kH * kH + kH * kOut;  // bf16 weight copy
 constexpr int kRows = 128;                            // particles per MLP block (4 waves x 32)
-constexpr int kMlpThreads = 256;                      // threads of the MLP forward and backward blocks
+constexpr int kMlpThreads = 256;                      // threads of the training forward's blocks
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -89,40 +89,89 @@ __device__ __forceinline__ int cell_of(float x, float y, float z, const CellGeo&
   return (cz * c.nc[1] + cy) * c.nc[0] + cx;
 }
 
-__global__ void k_cell_count(const float* __restrict__ ion_pos, const float* __restrict__ wc_pos, int64_t n_ion,
-                             int64_t n, int* __restrict__ count, CellGeo c) {
+// Counts the particles of every cell and keeps each one's arrival number in its
+// cell (rank), so that the scatter needs no atomics.  Neighbouring indices are
+// neighbours in space more often than not (the atoms of a molecule), so a run
+// of lanes in one cell shares one atomic.
+__global__ void __launch_bounds__(256) k_cell_count(const float* __restrict__ ion_pos, const float* __restrict__ wc_pos,
+                                                    int64_t n_ion, int64_t n, int* __restrict__ count,
+                                                    int* __restrict__ rank, CellGeo c) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float* r = (i < n_ion) ? ion_pos + 3 * i : wc_pos + 3 * (i - n_ion);
-  const float x = wrapf(r[0], c.L[0], c.invL[0]), y = wrapf(r[1], c.L[1], c.invL[1]),
-              z = wrapf(r[2], c.L[2], c.invL[2]);
-  atomicAdd(count + cell_of(x, y, z, c), 1);
+  const int lane = threadIdx.x & 63;
+  int cell = -1;
+  if (i < n) {
+    const float* r = (i < n_ion) ? ion_pos + 3 * i : wc_pos + 3 * (i - n_ion);
+    const float x = wrapf(r[0], c.L[0], c.invL[0]), y = wrapf(r[1], c.L[1], c.invL[1]),
+                z = wrapf(r[2], c.L[2], c.invL[2]);
+    cell = cell_of(x, y, z, c);
+  }
+  const int before = __shfl_up(cell, 1, 64);
+  const uint64_t heads = __ballot(lane == 0 || before != cell);  // first lanes of the runs
+  const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+  const uint64_t after = lane == 63 ? 0ull : heads >> (lane + 1);
+  const int len = after ? __ffsll((unsigned long long)after) : 64 - lane;  // of the run, at its head
+  int first = 0;
+  if (head == lane && cell >= 0) first = atomicAdd(count + cell, len);
+  first = __shfl(first, head, 64);
+  if (i < n) rank[i] = first + lane - head;
 }
 
-__global__ void k_cell_scatter(const float* __restrict__ ion_pos, const float* __restrict__ wc_pos,
-                               const float* __restrict__ ion_q, const float* __restrict__ wc_q, int64_t n_ion,
-                               int64_t n, int* __restrict__ cursor, float4* __restrict__ cpos,
-                               int* __restrict__ cidx, CellGeo c) {
+// Exclusive scan of the cell counts by several blocks: block b adds up the
+// counts before its tile by itself (reads that stream from L2), then scans the
+// tile; the last one also writes start[ncells].  Its work grows with the square
+// of the cell count, so larger grids keep the one-block scan (k_bin_scan).
+constexpr int kScanTile = 2048, kScanCells = 1 << 17;
+__global__ void __launch_bounds__(1024) k_cell_scan(const int* __restrict__ count, int* __restrict__ start,
+                                                    int ncells) {
+  __shared__ int red[16];
+  __shared__ int wsum[17];
+  __shared__ int vals[kScanTile];
+  const int t = threadIdx.x, b0 = blockIdx.x * kScanTile, nt = min(kScanTile, ncells - b0);
+  int s = 0;
+  for (int e = t; e < b0 / 4; e += 1024) {
+    const int4 v = reinterpret_cast<const int4*>(count)[e];
+    s += v.x + v.y + v.z + v.w;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if ((t & 63) == 0) red[t >> 6] = s;
+  const int total = block_exclusive_scan(count + b0, vals, nt, wsum);  // contains barriers
+  __syncthreads();
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) base += red[w];
+  for (int e = t; e < nt; e += 1024) start[b0 + e] = base + vals[e];
+  if (t == 0 && b0 + nt == ncells) start[ncells] = base + total;
+}
+
+__global__ void __launch_bounds__(256) k_cell_scatter(const float* __restrict__ ion_pos, const float* __restrict__ wc_pos,
+                                                      const float* __restrict__ ion_q, const float* __restrict__ wc_q,
+                                                      int64_t n_ion, int64_t n, const int* __restrict__ start,
+                                                      const int* __restrict__ rank, float4* __restrict__ cpos,
+                                                      int* __restrict__ cidx, CellGeo c) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const float* r = (i < n_ion) ? ion_pos + 3 * i : wc_pos + 3 * (i - n_ion);
   const float x = wrapf(r[0], c.L[0], c.invL[0]), y = wrapf(r[1], c.L[1], c.invL[1]),
               z = wrapf(r[2], c.L[2], c.invL[2]);
   const float q = (i < n_ion) ? ion_q[i] : wc_q[i - n_ion];
-  const int slot = atomicAdd(cursor + cell_of(x, y, z, c), 1);
+  const int slot = start[cell_of(x, y, z, c)] + rank[i];
   cpos[slot] = make_float4(x, y, z, q);
   cidx[slot] = (int)i;
 }
 
-// The atomic scatter leaves each cell's particles in arrival order; this puts
+// The scatter leaves each cell's particles in arrival order; this puts
 // them in order of original index (rank = number of the cell's particles
 // with a smaller index), so the cell order and every sum over neighbours
 // taken in it are the same on every call.  One thread per particle; a cell
-// holds tens of particles, so the O(n^2) ranking per cell is cheap.
+// holds tens of particles, so the O(n^2) ranking per cell is cheap.  Also clears
+// the cell counts for the next call.
 __global__ void k_cell_order(const float4* __restrict__ cpos_in, const int* __restrict__ cidx_in,
                              const int* __restrict__ start, int n,
-                             float4* __restrict__ cpos, int* __restrict__ cidx, CellGeo c) {
+                             float4* __restrict__ cpos, int* __restrict__ cidx, int* __restrict__ count,
+                             CellGeo c) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int k = e; k < c.ncells; k += gridDim.x * blockDim.x) count[k] = 0;
   if (e >= n) return;
   const float4 p = cpos_in[e];
   const int id = cidx_in[e];
@@ -644,7 +693,6 @@ __global__ void __launch_bounds__(kDescThreads, 4) k_descriptor(const float4* __
 constexpr int kPadIn = kIn + 4;     // 132: rows of 128 bf16
 constexpr int kPadH = kH + 4;       // 68: rows of 64 bf16
 constexpr int kPadO = kOut + 4;     // 36: rows of 32 bf16
-constexpr int kPadRows = kRows + 4; // 132: transposed tiles (rows = features, k = particles)
 
 // acc (32 x 32) += A (32 x K) * B (K x 32) with both operands k-contiguous:
 // A(m, k) = A[m * lda + k], B(k, n) = B[n * ldb + k].  One gfx950
@@ -696,8 +744,6 @@ __device__ __forceinline__ void mfma_tile_kc2(f32x16& acc0, f32x16& acc1, const 
 // weight offsets in the padded LDS copies
 constexpr int kLW1t = 0, kLW2t = kLW1t + kH * kPadIn, kLW3t = kLW2t + kH * kPadH,
               kLW4t = kLW3t + kH * kPadH, kLWt = kLW4t + kOut * kPadH;  // [out][in] copies
-constexpr int kLW1 = 0, kLW2 = kLW1 + kIn * kPadH, kLW3 = kLW2 + kH * kPadH, kLW4 = kLW3 + kH * kPadH,
-              kLW = kLW4 + kH * kPadO;                                   // [in][out] copies
 
 // ---------------------------------------------------------------------------
 // The correction of 32 particles per block in one pass: descriptor, network and
@@ -1098,157 +1144,265 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const unsigned short* __restric
 }
 
 // ---------------------------------------------------------------------------
-// MLP backward for one block of 128 particles: per-block partial gradients of
-// every weight and bias, written to gpart[block][kNTrain] (summed later in a
-// fixed order).  Weights are staged in LDS in their natural [in][out] layout
-// (the k of dh = dz W^T is the output index); the layer input and dz are
-// also kept transposed (features x particles) for dW = act^T dz, whose k is
-// the particle index.  dz / dz^T are double-buffered across layers.
+// MLP backward.  A block of 4 waves walks tiles of 64 particles and keeps the
+// gradients of all weights in registers over its tiles (18 tiles of 32 x 32, at
+// most 5 a wave), so one partial gradient per block is written, to
+// gpart[block][kNTrain] (summed by k_grad_update).  Per tile the layer inputs are
+// staged transposed (features x particles) and dz in both layouts:
+//   dW = act^T dz          contracts over the particles,
+//   dh^T = W dz^T          contracts over the layer's outputs; a lane ends with
+//                          four consecutive features of one particle.
+// dz / dz^T are double-buffered across layers.  All global loads of a tile are
+// 16 bytes a lane and issued before the first layer, the pre-activations
+// included.  (Blocks of 128 particles with 2-byte loads took 71 us at 4,512
+// particles, where 36 of them were all there were.)
 // ---------------------------------------------------------------------------
+constexpr int kBwdRows = 64;
+constexpr int kBwdThreads = 256;
+constexpr int kPadT = kBwdRows + 4;  // transposed tiles: rows of 64 particles
+constexpr int kBW2 = 0, kBW3 = kBW2 + kH * kPadH, kBW4 = kBW3 + kH * kPadH, kBW = kBW4 + kH * kPadO;
+
 struct BwdLds {
-  unsigned short w[kLW];                  // W1 [128][68], W2 [64][68], W3 [64][68], W4 [64][36]
-  unsigned short actT[kIn][kPadRows];     // layer input, transposed
-  unsigned short dz[2][kRows][kPadH];     // gradient at the layer output (bf16)
-  unsigned short dzT[2][kH][kPadRows];    // the same, transposed
+  unsigned short w[kBW];              // W2, W3, W4 as [in][out]
+  unsigned short xT[kIn][kPadT];      // network input, transposed
+  unsigned short hT[3][kH][kPadT];    // hidden layers, transposed
+  unsigned short dz[2][kBwdRows][kPadH];  // gradient at the layer output (bf16)
+  unsigned short dzT[2][kH][kPadT];   // the same, transposed
 };
 
-__global__ void __launch_bounds__(256) k_mlp_bwd(const unsigned short* __restrict__ X, const float* __restrict__ Z,
-                                                 const unsigned short* __restrict__ H, const float* __restrict__ dC,
-                                                 int n, const unsigned short* __restrict__ w_g,
-                                                 float* __restrict__ gpart) {
+// 8 consecutive features f.. of particle r into a transposed tile
+__device__ __forceinline__ void put_transposed(unsigned short (*tile)[kPadT], int f, int r, uint4 v) {
+  const unsigned u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    tile[f + 2 * e][r] = (unsigned short)u[e];
+    tile[f + 2 * e + 1][r] = (unsigned short)(u[e] >> 16);
+  }
+}
+
+__global__ void __launch_bounds__(kBwdThreads) k_mlp_bwd(const unsigned short* __restrict__ X,
+                                                         const float* __restrict__ Z,
+                                                         const unsigned short* __restrict__ H,
+                                                         const float* __restrict__ dC, int n,
+                                                         const unsigned short* __restrict__ w_g,
+                                                         float* __restrict__ gpart) {
   extern __shared__ __align__(16) unsigned char smem[];
   BwdLds& S = *reinterpret_cast<BwdLds*>(smem);
-  const int row0 = blockIdx.x * kRows;
-  const int tid = threadIdx.x, wave = tid >> 6;
-  float* gp = gpart + (size_t)blockIdx.x * kNTrain;
+  const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, kh = l >> 5;
+  // weights, 8 outputs of one input at a time
   {
-    const int rows[4] = {kIn, kH, kH, kH}, cols[4] = {kH, kH, kH, kOut};
-    const int gofs[4] = {0, kIn * kH, kIn * kH + kH * kH, kIn * kH + 2 * kH * kH};
-    const int lofs[4] = {kLW1, kLW2, kLW3, kLW4}, pitch[4] = {kPadH, kPadH, kPadH, kPadO};
+    constexpr int kChunks = (2 * kH * kH + kH * kOut) / 8;
 #pragma unroll
-    for (int L = 0; L < 4; ++L)
-      for (int e = tid; e < rows[L] * cols[L]; e += blockDim.x) {
-        const int r = e / cols[L], c = e - r * cols[L];
-        S.w[lofs[L] + r * pitch[L] + c] = w_g[gofs[L] + e];
+    for (int c = tid; c < kChunks; c += kBwdThreads) {
+      const uint4 v = reinterpret_cast<const uint4*>(w_g + kIn * kH)[c];
+      const int e = 8 * c;
+      int r, col, at;
+      if (e < 2 * kH * kH) { r = (e / kH) % kH; col = e % kH; at = (e < kH * kH ? kBW2 : kBW3) + r * kPadH + col; }
+      else { r = (e - 2 * kH * kH) / kOut; col = e % kOut; at = kBW4 + r * kPadO + col; }
+      uint2* dst = reinterpret_cast<uint2*>(S.w + at);
+      dst[0] = make_uint2(v.x, v.y);
+      dst[1] = make_uint2(v.z, v.w);
+    }
+  }
+  f32x16 g1[2], g2, g3, g4;  // this wave's tiles of dW1 (2 of 8), dW2, dW3 (1 of 4), dW4 (waves 0, 1)
+  zero(g1[0]); zero(g1[1]); zero(g2); zero(g3); zero(g4);
+  float gb[4] = {0.f, 0.f, 0.f, 0.f};  // bias sums of output tid / 4, a quarter of the particles
+  // dh tile of this wave: inputs 32 (wave % 2).., particles 32 (wave / 2)..
+  const int f0 = 32 * (wave & 1), r0 = 32 * (wave >> 1);
+  const int ntiles = (n + kBwdRows - 1) / kBwdRows;
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int row0 = tile * kBwdRows;
+    // loads: particle tid % 64 and its features (tid / 64) * 8 + 32 u ..; the
+    // pre-activations of the dh tile
+    const int lr = tid & 63, row = min(row0 + lr, n - 1);
+    const bool in = row0 + lr < n;
+    uint4 xv[4], hv[3][2];
+    float4 cv[2], zv[3][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) xv[u] = reinterpret_cast<const uint4*>(X + (size_t)row * kIn)[wave + 4 * u];
+#pragma unroll
+    for (int L = 0; L < 3; ++L)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        hv[L][u] = reinterpret_cast<const uint4*>(H + ((size_t)L * n + row) * kH)[wave + 4 * u];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) cv[u] = reinterpret_cast<const float4*>(dC + (size_t)row * kOut)[2 * wave + u];
+    const int zrow = min(row0 + r0 + (l & 31), n - 1);
+    const bool zin = row0 + r0 + (l & 31) < n;
+#pragma unroll
+    for (int L = 0; L < 3; ++L)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        zv[L][q] = *reinterpret_cast<const float4*>(Z + ((size_t)L * n + zrow) * kH + f0 + 8 * q + 4 * kh);
+    __syncthreads();  // the previous tile is done with the staged arrays
+    // particles past n: their dz is zero, whatever the inputs hold
+#pragma unroll
+    for (int u = 0; u < 4; ++u) put_transposed(S.xT, 8 * (wave + 4 * u), lr, xv[u]);
+#pragma unroll
+    for (int L = 0; L < 3; ++L)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) put_transposed(S.hT[L], 8 * (wave + 4 * u), lr, hv[L][u]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float c4[4] = {cv[u].x, cv[u].y, cv[u].z, cv[u].w};
+      unsigned short b4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        b4[e] = in ? f2bf(c4[e]) : (unsigned short)0;
+        S.dzT[0][8 * wave + 4 * u + e][lr] = b4[e];
       }
-  }
-  // dz <- dC (bf16, zero for rows past n), both layouts
-  for (int e = tid; e < kRows * kOut; e += blockDim.x) {
-    const int r = e / kOut, k = e % kOut;
-    const unsigned short v = (row0 + r < n) ? f2bf(dC[(size_t)(row0 + r) * kOut + k]) : (unsigned short)0;
-    S.dz[0][r][k] = v;
-    S.dzT[0][k][r] = v;
-  }
-  const int offW[4] = {kLW1, kLW2, kLW3, kLW4};
-  const int pitW[4] = {kPadH, kPadH, kPadH, kPadO};
-  const int offGW[4] = {kOffW1, kOffW2, kOffW3, kOffW4};
-  const int offGB[4] = {kOffB1, kOffB2, kOffB3, kOffB4};
-  const int nin[4] = {kIn, kH, kH, kH};
-  const int nout[4] = {kH, kH, kH, kOut};
-  int cur = 0;
-  for (int layer = 3; layer >= 0; --layer) {
-    const int ni = nin[layer], no = nout[layer];
-    // layer input activation (x for layer 0, h_layer otherwise), transposed
-    for (int e = tid; e < kRows * ni; e += blockDim.x) {
-      const int k = e / kRows, r = e - k * kRows;
-      unsigned short v = 0;
-      if (row0 + r < n) v = layer == 0 ? X[(size_t)(row0 + r) * kIn + k] : H[((size_t)(layer - 1) * n + row0 + r) * kH + k];
-      S.actT[k][r] = v;
+      *reinterpret_cast<ushort4*>(&S.dz[0][lr][8 * wave + 4 * u]) = make_ushort4(b4[0], b4[1], b4[2], b4[3]);
     }
     __syncthreads();
-    // weight gradient tiles: dW (ni x no) = act^T (ni x rows) * dz (rows x no)
-    const int tm = ni / 32, tn = no / 32;
-    for (int t = wave; t < tm * tn; t += 4) {
-      const int mi = t / tn, nj = t % tn;
-      f32x16 acc;
-      zero(acc);
-      mfma_tile_kc(acc, &S.actT[mi * 32][0], kPadRows, &S.dzT[cur][nj * 32][0], kPadRows, kRows);
+    // bias gradient of the layer whose dz is in buffer `cur`: output tid / 4
+    auto bias = [&](int cur, int no, float& sum) {
+      const int col = tid >> 2;
+      if (col < no) {
+        const unsigned short* z = &S.dzT[cur][col][(tid & 3) * 16];
+        float s = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        gp[offGW[layer] + (mi * 32 + acc_row(r)) * no + nj * 32 + acc_col()] = acc[r];
-    }
-    // bias gradient: sums of dz over particles (fixed order)
-    for (int col = tid; col < no; col += blockDim.x) {
-      float s = 0.0f;
-      for (int r = 0; r < kRows; ++r) s += bf2f(S.dzT[cur][col][r]);
-      gp[offGB[layer] + col] = s;
-    }
-    if (layer == 0) break;
-    // gradient to the layer below: dh (rows x ni) = dz (rows x no) * W^T, then * silu'(z)
-    const int nxt = cur ^ 1;
-    for (int t = wave; t < (kRows / 32) * (ni / 32); t += 4) {
-      const int ri = t / (ni / 32), mj = t % (ni / 32);
-      f32x16 acc;
-      zero(acc);
-      // A(m, k) = dz[r0 + m][k], B(k, n) = W[m0 + n][k]  (W stored [in][out])
-      mfma_tile_kc(acc, &S.dz[cur][ri * 32][0], kPadH, S.w + offW[layer] + mj * 32 * pitW[layer], pitW[layer], no);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = ri * 32 + acc_row(r), col = mj * 32 + acc_col();
-        float v = 0.0f;
-        if (row0 + row < n) v = acc[r] * dsilu(Z[((size_t)(layer - 1) * n + row0 + row) * kH + col]);
-        const unsigned short b = f2bf(v);
-        S.dz[nxt][row][col] = b;
-        S.dzT[nxt][col][row] = b;
+        for (int r = 0; r < 16; ++r) s += bf2f(z[r]);
+        sum += s;
       }
-    }
+    };
+    // dh of the layer below: (inputs x particles) = W dz^T, times silu'(z), into
+    // buffer `nxt`
+    auto back = [&](int cur, int nxt, const unsigned short* W, int pitch, int K, const float4 (&z)[4]) {
+      f32x16 a;
+      zero(a);
+      mfma_tile_kc(a, W + f0 * pitch, pitch, &S.dz[cur][r0][0], kPadH, K);
+      const int r = r0 + (l & 31);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float z4[4] = {z[q].x, z[q].y, z[q].z, z[q].w};
+        const int f = f0 + 8 * q + 4 * kh;
+        unsigned short b4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          b4[e] = zin ? f2bf(a[4 * q + e] * dsilu(z4[e])) : (unsigned short)0;
+          S.dzT[nxt][f + e][r] = b4[e];
+        }
+        *reinterpret_cast<ushort4*>(&S.dz[nxt][r][f]) = make_ushort4(b4[0], b4[1], b4[2], b4[3]);
+      }
+    };
+    // output layer
+    if (wave < 2) mfma_tile_kc(g4, &S.hT[2][32 * wave][0], kPadT, &S.dzT[0][0][0], kPadT, kBwdRows);
+    bias(0, kOut, gb[3]);
+    back(0, 1, S.w + kBW4, kPadO, 32, zv[2]);
     __syncthreads();
-    cur = nxt;
+    // third and second hidden layer: dW tile (inputs 32 (wave / 2).., outputs 32 (wave % 2)..)
+    mfma_tile_kc(g3, &S.hT[1][32 * (wave >> 1)][0], kPadT, &S.dzT[1][32 * (wave & 1)][0], kPadT, kBwdRows);
+    bias(1, kH, gb[2]);
+    back(1, 0, S.w + kBW3, kPadH, 64, zv[1]);
+    __syncthreads();
+    mfma_tile_kc(g2, &S.hT[0][32 * (wave >> 1)][0], kPadT, &S.dzT[0][32 * (wave & 1)][0], kPadT, kBwdRows);
+    bias(0, kH, gb[1]);
+    back(0, 1, S.w + kBW2, kPadH, 64, zv[0]);
+    __syncthreads();
+    // first hidden layer: inputs 32 wave .., both halves of the outputs
+    mfma_tile_kc2(g1[0], g1[1], &S.xT[32 * wave][0], kPadT, &S.dzT[1][0][0], &S.dzT[1][32][0], kPadT, kBwdRows);
+    bias(1, kH, gb[0]);
+  }
+  float* gp = gpart + (size_t)blockIdx.x * kNTrain;
+  auto put = [&](const f32x16& a, int ofs, int i0, int o0, int no) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) gp[ofs + (i0 + acc_row(r)) * no + o0 + acc_col()] = a[r];
+  };
+  put(g1[0], kOffW1, 32 * wave, 0, kH);
+  put(g1[1], kOffW1, 32 * wave, 32, kH);
+  put(g2, kOffW2, 32 * (wave >> 1), 32 * (wave & 1), kH);
+  put(g3, kOffW3, 32 * (wave >> 1), 32 * (wave & 1), kH);
+  if (wave < 2) put(g4, kOffW4, 32 * wave, 0, kOut);
+  const int offB[4] = {kOffB1, kOffB2, kOffB3, kOffB4};
+#pragma unroll
+  for (int L = 0; L < 4; ++L) {
+    float s = gb[L];
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if ((tid & 3) == 0 && (tid >> 2) < (L == 3 ? kOut : kH)) gp[offB[L] + (tid >> 2)] = s;
   }
 }
 
-// Sum of the per-block gradient partials in block order (deterministic) and
-// of the loss partials; gscale_loss converts the squared-error sum to the mean.
-__global__ void k_grad_reduce(const float* __restrict__ gpart, int nblk, float* __restrict__ grad,
-                              const double* __restrict__ loss_part, int nloss, double loss_scale,
-                              double* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// Stores the bf16 copies of weight e (dense index over the four layers): [in][out],
+// [out][in], and in the order in which k_correction's waves read them as MFMA
+// fragments (lane l of fragment (tile of 32 outputs, step of 16 inputs) holds
+// output l % 32, inputs 8 (l / 32) + 0..7).
+struct WeightCopies {
+  unsigned short *w, *wt, *wf;
+};
+__device__ __forceinline__ void store_weight(const WeightCopies& W, int e, float value) {
+  int off = 0, ni = kIn, no = kH;
+  if (e < kIn * kH) { off = 0; ni = kIn; no = kH; }
+  else if (e < kIn * kH + kH * kH) { off = kIn * kH; ni = kH; no = kH; }
+  else if (e < kIn * kH + 2 * kH * kH) { off = kIn * kH + kH * kH; ni = kH; no = kH; }
+  else { off = kIn * kH + 2 * kH * kH; ni = kH; no = kOut; }
+  const int loc = e - off, i = loc / no, o = loc % no;
+  const unsigned short b = f2bf(value);
+  W.w[e] = b;
+  W.wt[off + o * ni + i] = b;
+  const int frag = (o >> 5) * (ni / 16) + (i >> 4), lane = (o & 31) + 32 * ((i >> 3) & 1);
+  W.wf[off + (frag * 64 + lane) * 8 + (i & 7)] = b;
+}
+// dense weight index of parameter p, or -1 (a bias)
+__device__ __forceinline__ int weight_of_param(int p) {
+  if (p < kOffB1) return p;
+  if (p >= kOffW2 && p < kOffB2) return p - kOffW2 + kIn * kH;
+  if (p >= kOffW3 && p < kOffB3) return p - kOffW3 + kIn * kH + kH * kH;
+  if (p >= kOffW4 && p < kOffB4) return p - kOffW4 + kIn * kH + 2 * kH * kH;
+  return -1;
+}
+
+// The gradient from the per-block partials (fixed order: four quarters of the
+// blocks, then the quarters), the mean loss, and, with an update, Adam on the
+// FP32 master parameters and their bf16 copies.  64 parameters per block of 256.
+struct AdamStep {
+  int on;
+  float lr, b1, b2, eps, c1, c2;
+};
+__global__ void __launch_bounds__(256) k_grad_update(const float* __restrict__ gpart, int nblk,
+                                                     float* __restrict__ grad_out,
+                                                     const double* __restrict__ loss_part, int nloss,
+                                                     double loss_scale, double* __restrict__ loss, AdamStep ad,
+                                                     float* __restrict__ params, float* __restrict__ m,
+                                                     float* __restrict__ v, WeightCopies W) {
+  __shared__ float part[4][64];
+  const int lane = threadIdx.x & 63, quarter = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + lane;
+  const int per = (nblk + 3) / 4, b0 = min(nblk, quarter * per), b1 = min(nblk, b0 + per);
+  float s = 0.0f;
   if (p < kNTrain) {
-    float s = 0.0f;
-    for (int b = 0; b < nblk; ++b) s += gpart[(size_t)b * kNTrain + p];
-    grad[p] = s;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += gpart[(size_t)b * kNTrain + p];
   }
-  if (p == 0 && loss) {
-    double s = 0.0;
-    for (int b = 0; b < nloss; ++b) s += loss_part[b];
-    *loss = s * loss_scale;
+  part[quarter][lane] = s;
+  __syncthreads();
+  if (quarter == 0 && p < kNTrain) {
+    const float g = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+    if (grad_out) grad_out[p] = g;
+    if (ad.on) {
+      const float mm = ad.b1 * m[p] + (1.0f - ad.b1) * g;
+      const float vv = ad.b2 * v[p] + (1.0f - ad.b2) * g * g;
+      m[p] = mm;
+      v[p] = vv;
+      const float x = params[p] - ad.lr * (mm / ad.c1) / (sqrtf(vv / ad.c2) + ad.eps);
+      params[p] = x;
+      const int e = weight_of_param(p);
+      if (e >= 0) store_weight(W, e, x);
+    }
+  }
+  if (blockIdx.x == 0 && quarter == 1 && loss) {  // one wave adds the loss partials
+    double t = 0.0;
+    for (int b = lane; b < nloss; b += 64) t += loss_part[b];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if (lane == 0) *loss = t * loss_scale;
   }
 }
 
-// Adam on the FP32 master parameters, then bf16 copies of the weights in
-// both layouts ([in][out] for backward, [out][in] for forward).
-__global__ void k_adam(float* __restrict__ params, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ grad, float lr, float b1, float b2, float eps, float c1, float c2) {
+__global__ void k_weights_to_bf16(const float* __restrict__ params, WeightCopies W) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= kNTrain) return;
-  const float g = grad[p];
-  const float mm = b1 * m[p] + (1.0f - b1) * g;
-  const float vv = b2 * v[p] + (1.0f - b2) * g * g;
-  m[p] = mm;
-  v[p] = vv;
-  params[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-}
-
-// bf16 copies of the weights: [in][out], [out][in], and in the order in which
-// k_correction's waves read them as MFMA fragments (lane l of fragment (tile of
-// 32 outputs, step of 16 inputs) holds output l % 32, inputs 8 (l / 32) + 0..7).
-__global__ void k_weights_to_bf16(const float* __restrict__ params, unsigned short* __restrict__ w,
-                                  unsigned short* __restrict__ wt, unsigned short* __restrict__ wf) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= kNWeights) return;
-  // locate layer
-  int off = 0, pofs = 0, ni = kIn, no = kH;
-  if (e < kIn * kH) { off = 0; pofs = kOffW1; ni = kIn; no = kH; }
-  else if (e < kIn * kH + kH * kH) { off = kIn * kH; pofs = kOffW2; ni = kH; no = kH; }
-  else if (e < kIn * kH + 2 * kH * kH) { off = kIn * kH + kH * kH; pofs = kOffW3; ni = kH; no = kH; }
-  else { off = kIn * kH + 2 * kH * kH; pofs = kOffW4; ni = kH; no = kOut; }
-  const int loc = e - off;
-  const int i = loc / no, o = loc % no;
-  const unsigned short b = f2bf(params[pofs + loc]);
-  w[e] = b;                      // [in][out]
-  wt[off + o * ni + i] = b;      // [out][in]
-  const int frag = (o >> 5) * (ni / 16) + (i >> 4), lane = (o & 31) + 32 * ((i >> 3) & 1);
-  wf[off + (frag * 64 + lane) * 8 + (i & 7)] = b;
+  const int e = weight_of_param(p);
+  if (e >= 0) store_weight(W, e, params[p]);
 }
 
 }  // namespace mlp

@@ -24,6 +24,10 @@ def _system(n, box, seed, clump):
     if clump:  # half of the particles in two balls, one of them around the box corner
         k = n // 2
         pos[:k] = (rng.normal(0.0, 1.2, (k, 3)) + np.where(rng.random((k, 1)) < 0.5, 0.0, 0.5 * box)) % box
+    if box[0] > 200.0:
+        # coordinates of 10 binary places: their FP32 differences are exact (a
+        # coordinate rounding of 1e-5 A is 5e-5 of such a dense descriptor)
+        pos = np.round(pos * 1024.0) / 1024.0 % box
     pos = np.minimum(pos.astype(np.float32), np.nextafter(np.float32(box), np.float32(0))).astype(np.float64)
     q = rng.choice([6.0, 1.0, -8.0], n)
     return pos, q
@@ -44,6 +48,8 @@ def _neighbours(pos, box, rc):
     (31, (12.5, 12.5, 12.5), False), (33, (12.5, 21.0, 16.5), False), (257, (17.0, 12.5, 30.0), False),
     (1000, (12.5, 12.5, 12.5), False),      # about 137 neighbours: three lists
     (900, (20.0, 16.5, 24.5), True),        # lists of very different lengths in one wave
+    (700, (64.0, 52.0, 40.0), True),        # 2,080 cells: two tiles of the cell scan
+    (300, (256.0, 256.0, 256.0), True),     # 262,144 cells: the one-block scan
 ])
 def test_descriptor_and_correction_match_oracle(torch, n, box, clump):
     from paper_2504_15508_amd import learned as L
