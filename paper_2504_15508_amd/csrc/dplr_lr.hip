@@ -75,6 +75,7 @@ static_assert(DPLR_SORT_CHUNKS >= 1 && DPLR_SORT_CHUNKS <= 256, "sort chunk coun
 #define DPLR_FFTZ_COLS 8
 #endif
 
+constexpr int kSmallSortBins = 4096;  // bins of the one-block sort (its scan and publication)
 constexpr int kMinMesh = 16;
 constexpr int kMaxMesh = 512;
 constexpr int kMaxOrder = 8;
@@ -161,6 +162,7 @@ struct dplr_lr_plan_s {
   size_t lds_spread = 0, lds_ffty = 0, lds_z = 0, lds_ifftx = 0, lds_ixy = 0;
   bool plane = false;         // whole z planes fit in LDS: spread + x and y transforms in one kernel
   bool ixy = false;           // inverse y and x transforms of a plane component in one kernel
+  int last_split = 1;         // particle splits of the last compute
   int nzout = 3;              // spectra out of the z pass: three components, A and B, or the potential
   bool mixed = false;         // mesh outside the tuned kernels: mixed-radix path
   long long* mmesh = nullptr; // mixed-radix path: fixed-point mesh [Kz][Ky][Kx]
@@ -228,13 +230,14 @@ hipEvent_t prof_event(dplr_lr_plan p) {
   return e;
 }
 
-// Records an event pair around one kernel launch when instrumentation is on.
+// Records an event pair around one kernel launch when instrumentation is on
+// (stage < 0: the launch belongs to an enclosing scope).
 struct ProfScope {
   dplr_lr_plan p;
   int stage;
   hipEvent_t a = nullptr;
   ProfScope(dplr_lr_plan p_, int s) : p(p_), stage(s) {
-    if (p->prof) {
+    if (p->prof && stage >= 0) {
       a = prof_event(p);
       (void)hipEventRecord(a, p->stream);
     }
@@ -269,6 +272,7 @@ bool choose_geometry(dplr_lr_plan p) {
   const int P = p->cfg.order;
   const size_t ts = p->tsize, cs = 2 * ts;
   g.K[0] = Kx; g.K[1] = Ky; g.K[2] = Kz;
+  for (int a = 0; a < 3; ++a) g.invK[a] = 1.0 / g.K[a];
   g.Kh = Kx / 2 + 1;
   g.qshift = 2;
   g.split_by_index = 0;
@@ -469,13 +473,71 @@ void set_lds_attrs(dplr_lr_plan p) {
   if (p->ixy) attr((const void*)k_ifft_xy<T>, p->lds_ixy);
 }
 
+// Counting sort of the particles into the bins of g without global atomics:
+// one block for few particles, otherwise a histogram per chunk of particles, the
+// chunk offsets, and the placement (which adds up few histograms itself).
+// Returns the number of charge-maximum words written.
+template <typename T, int P>
+int launch_sort(dplr_lr_plan p, const Geo& g, const T* ip, const T* iq, const T* wp, const T* wq, int64_t n_ion,
+                int64_t n, const double ih[3], T4<T>* sorted, int* sidx, const int stage[3]) {
+  hipStream_t s = p->stream;
+  const size_t lds = sizeof(int) * g.nbins;
+  if (n == 0) {
+    ProfScope ps(p, stage[1]);
+    hipLaunchKernelGGL(k_fill_int, dim3((g.nbins + 1 + 255) / 256), dim3(256), 0, s, p->bin_start, g.nbins + 1, 0);
+    return 0;
+  }
+  if (n <= kSmallSort && g.nbins <= kSmallSortBins) {
+    ProfScope ps(p, stage[2]);
+    hipLaunchKernelGGL((k_sort_small<T, P>), dim3(1), dim3(1024), 2 * lds, s, ip, wp, iq, wq, n_ion, n, ih[0], ih[1],
+                       ih[2], p->bin_start, sorted, sidx, p->perm, p->qmax, g);
+    return 1;
+  }
+  // chunk size: a multiple of DPLR_SORT_CHUNK_ALIGN, at most max_chunks chunks,
+  // and few of them where that saves the column scan
+  constexpr int64_t ca = DPLR_SORT_CHUNK_ALIGN, few = 1024;
+  const int64_t chunk = n <= few * kPlaceScanChunks && g.nbins <= kPlaceScanBins
+                            ? few
+                            : std::max<int64_t>(ca, ((n + p->max_chunks - 1) / p->max_chunks + ca - 1) / ca * ca);
+  const int nblk = (int)((n + chunk - 1) / chunk);
+  {
+    ProfScope ps(p, stage[0]);
+    hipLaunchKernelGGL((k_bin_hist<T, P>), dim3(nblk), dim3(1024), lds, s, ip, wp, n_ion, n, ih[0], ih[1], ih[2],
+                       p->bin_hist, (int)chunk, g);
+  }
+  if (nblk > kPlaceScanChunks || g.nbins > kPlaceScanBins) {
+    ProfScope ps(p, stage[1]);
+    hipLaunchKernelGGL(k_bin_colscan, dim3((g.nbins + 63) / 64), dim3(1024), 0, s, p->bin_hist, p->bin_count, nblk,
+                       g.nbins);
+  }
+  {
+    ProfScope ps(p, stage[2]);
+    hipLaunchKernelGGL((k_bin_place<T, P>), dim3(nblk), dim3(1024), 2 * lds, s, ip, wp, iq, wq, n_ion, n, ih[0],
+                       ih[1], ih[2], p->bin_hist, p->bin_count, p->bin_start, sorted, sidx, p->perm, p->qmax,
+                       (int)chunk, g);
+  }
+  return nblk;
+}
+
 template <typename T, int P>
 dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, const void* ion_q, int64_t n_wc,
                            const void* wc_pos, const void* wc_q, void* ion_force, void* wc_force, double* energy,
                            double* virial) {
-  const Geo& g = p->geo;
   hipStream_t s = p->stream;
   const int64_t n = n_ion + n_wc;
+  Geo g = p->geo;
+  if (p->plane && p->fp64) {
+    // FP64 plans split the particles no further than a spread block of 1024
+    // threads has visits for: every split is one more partial plane to transform
+    // and add (FP32 plans keep the mesh's split, whose rounding their results
+    // carry).  256 particles on 32^3: spread 11.2, z pass 15.9 us with 8 splits,
+    // 10.0 and 10.2 with 1.
+    int split = 1;
+    while (split < g.nsplit && n * P > (int64_t)1024 * g.K[2] * split) split *= 2;
+    g.nsplit = split;
+    g.nbins = split * g.K[2] * g.NQ;
+  }
+  p->last_split = g.nsplit;
   const double ih[3] = {g.K[0] / p->box[0], g.K[1] / p->box[1], g.K[2] / p->box[2]};
   const cpx<T>* tw = reinterpret_cast<const cpx<T>*>(p->twiddle);
   T4<T>* sorted = reinterpret_cast<T4<T>*>(p->sorted);
@@ -487,34 +549,8 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
 
   int nqpart = 1;  // charge-maximum words the spread reads
   if (p->block_hist) {
-    // chunk size: a multiple of DPLR_SORT_CHUNK_ALIGN, at most max_chunks chunks
-    constexpr int64_t ca = DPLR_SORT_CHUNK_ALIGN;
-    int64_t chunk = std::max<int64_t>(ca, ((n + p->max_chunks - 1) / p->max_chunks + ca - 1) / ca * ca);
-    const int nblk = (int)((n + chunk - 1) / chunk);
-    const size_t lds = sizeof(int) * g.nbins;
-    if (n > 0) {
-      ProfScope ps(p, 0);
-      hipLaunchKernelGGL((k_bin_hist<T, P>), dim3(nblk), dim3(1024), lds, s, ip, wp, n_ion, n, ih[0], ih[1], ih[2],
-                         p->bin_hist, (int)chunk, g);
-    }
-    {
-      ProfScope ps(p, 1);
-      // per-bin chunk offsets and bin totals; the placement scans the totals
-      if (n > 0) {
-        hipLaunchKernelGGL(k_bin_colscan, dim3((g.nbins + 63) / 64), dim3(1024), 0, s, p->bin_hist, p->bin_count,
-                           nblk, g.nbins);
-      } else {
-        hipLaunchKernelGGL(k_fill_int, dim3((g.nbins + 1 + 255) / 256), dim3(256), 0, s, p->bin_start, g.nbins + 1,
-                           0);
-      }
-    }
-    if (n > 0) {
-      ProfScope ps(p, 2);
-      hipLaunchKernelGGL((k_bin_place<T, P>), dim3(nblk), dim3(1024), 2 * lds, s, ip, wp, (const T*)ion_q,
-                         (const T*)wc_q, n_ion, n, ih[0], ih[1], ih[2], p->bin_hist, p->bin_count, p->bin_start,
-                         sorted, p->sidx, p->perm, p->qmax, (int)chunk, g);
-    }
-    nqpart = n > 0 ? nblk : 0;
+    const int stage[3] = {0, 1, 2};
+    nqpart = launch_sort<T, P>(p, g, ip, (const T*)ion_q, wp, (const T*)wc_q, n_ion, n, ih, sorted, p->sidx, stage);
   } else {
     if (n > 0) {
       const int nb = (int)((n + 255) / 256);
@@ -535,8 +571,13 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
     }
   }
   if (p->plane) {
+    // small planes with few visits a block take fewer threads (their barriers
+    // wait for fewer waves): 256 at least, and 16 mesh points a thread at most
+    const int64_t visits = n * P / ((int64_t)g.K[2] * g.nsplit);
+    int thr = visits > 512 ? 1024 : visits > 128 ? 512 : 256;
+    while (thr < 1024 && g.K[0] * g.K[1] > 16 * thr) thr *= 2;
     ProfScope ps(p, 9);
-    hipLaunchKernelGGL((k_spread_xy<T, P>), dim3(g.K[2] * g.nsplit), dim3(p->thr_spread), p->lds_spread, s, sorted,
+    hipLaunchKernelGGL((k_spread_xy<T, P>), dim3(g.K[2] * g.nsplit), dim3(thr), p->lds_spread, s, sorted,
                        p->sidx, p->bin_start, (const unsigned*)p->qmax, nqpart, spec, nspec, tw, g);
   } else {
     {
@@ -567,7 +608,7 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
   const bool want_virial = !(p->cfg.flags & DPLR_LR_NO_VIRIAL) && virial;
   if (p->ixy) {
     ProfScope ps(p, 10);
-    hipLaunchKernelGGL((k_ifft_xy<T>), dim3(ncomp * g.K[2]), dim3(p->thr_ixy), p->lds_ixy, s, fspec,
+    hipLaunchKernelGGL((k_ifft_xy<T>), dim3(ncomp * g.K[2] + 1), dim3(p->thr_ixy), p->lds_ixy, s, fspec,
                        reinterpret_cast<T*>(p->field), ncomp, xpad, tw, g, (const double*)p->partials,
                        p->cfg.coulomb_k / (2.0 * V), energy, want_virial ? virial : (double*)nullptr);
   } else {
@@ -688,27 +729,13 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
     Geo gs = g;
     gs.nsplit = S;
     gs.nbins = S * g.K[2] * g.NQ;
-    const int64_t ca = DPLR_SORT_CHUNK_ALIGN;
-    const int64_t chunk = std::max<int64_t>(ca, ((n + p->max_chunks - 1) / p->max_chunks + ca - 1) / ca * ca);
-    const int nblk = (int)((n + chunk - 1) / chunk);
-    const size_t lds = sizeof(int) * gs.nbins;
-    if (n > 0) {
-      hipLaunchKernelGGL((k_bin_hist<T, P>), dim3(nblk), dim3(1024), lds, s, (const T*)ion_pos, (const T*)wc_pos,
-                         n_ion, n, ih[0], ih[1], ih[2], p->bin_hist, (int)chunk, gs);
-      hipLaunchKernelGGL(k_bin_colscan, dim3((gs.nbins + 63) / 64), dim3(1024), 0, s, p->bin_hist, p->bin_count,
-                         nblk, gs.nbins);
-      hipLaunchKernelGGL((k_bin_place<T, P>), dim3(nblk), dim3(1024), 2 * lds, s, (const T*)ion_pos,
-                         (const T*)wc_pos, (const T*)ion_q, (const T*)wc_q, n_ion, n, ih[0], ih[1], ih[2],
-                         p->bin_hist, p->bin_count, p->bin_start, (T4<T>*)p->mrec, p->mspk, p->perm, p->qmax,
-                         (int)chunk, gs);
-    } else {
-      hipLaunchKernelGGL(k_fill_int, dim3((gs.nbins + 1 + 255) / 256), dim3(256), 0, s, p->bin_start, gs.nbins + 1,
-                         0);
-    }
+    const int stage[3] = {-1, -1, -1};
+    const int nqpart = launch_sort<T, P>(p, gs, (const T*)ion_pos, (const T*)ion_q, (const T*)wc_pos, (const T*)wc_q,
+                                         n_ion, n, ih, (T4<T>*)p->mrec, p->mspk, stage);
     if (fused)
       hipLaunchKernelGGL((k_mixed_spread_xy<T, P>), dim3(g.K[2], S), dim3(1024), p->mfused, s,
                          (const T4<T>*)p->mrec, (const int*)p->mspk, (const int*)p->bin_start, gs,
-                         (const unsigned*)p->qmax, n > 0 ? nblk : 0, reinterpret_cast<cpx<T>*>(p->mmesh));
+                         (const unsigned*)p->qmax, nqpart, reinterpret_cast<cpx<T>*>(p->mmesh));
     else
       hipLaunchKernelGGL((k_mixed_spread_sorted<T, P>), dim3(g.K[2], S), dim3(1024), p->lds_mplane, s,
                          (const T4<T>*)p->mrec, (const int*)p->mspk, (const int*)p->bin_start, gs, spec, p->mmesh);
@@ -927,7 +954,10 @@ dplr_lr_status dplr_lr_plan_create(const dplr_lr_config* cfg, void* hip_stream, 
   if (!tuned_mesh(cfg->mesh)) {
     p->mixed = true;
     Geo& g = p->geo;
-    for (int a = 0; a < 3; ++a) g.K[a] = cfg->mesh[a];
+    for (int a = 0; a < 3; ++a) {
+      g.K[a] = cfg->mesh[a];
+      g.invK[a] = 1.0 / g.K[a];
+    }
     g.Kh = g.K[0] / 2 + 1;
     const size_t ts = p->tsize, cs = 2 * ts;
     const size_t ntot = (size_t)g.K[0] * g.K[1] * g.K[2];
@@ -1146,17 +1176,15 @@ dplr_lr_status dplr_lr_scale_grad(dplr_lr_plan p, const double* grad_energy, int
   if (n_ion < 0 || n_wc < 0) return fail(p, DPLR_LR_E_INVALID, "negative particle count");
   if (n_ion > 0 && (!ion_force || !ion_grad)) return fail(p, DPLR_LR_E_INVALID, "ion pointer is NULL");
   if (n_wc > 0 && (!wc_force || !wc_grad)) return fail(p, DPLR_LR_E_INVALID, "wc pointer is NULL");
-  const int64_t m[2] = {3 * n_ion, 3 * n_wc};
-  const void* src[2] = {ion_force, wc_force};
-  void* dst[2] = {ion_grad, wc_grad};
-  for (int i = 0; i < 2; ++i) {
-    if (m[i] == 0) continue;
-    const unsigned nb = (unsigned)((m[i] + 255) / 256);
-    if (p->fp64)
-      hipLaunchKernelGGL(k_scale_grad<double>, dim3(nb), dim3(256), 0, p->stream, grad_energy, (const double*)src[i], (double*)dst[i], m[i]);
-    else
-      hipLaunchKernelGGL(k_scale_grad<float>, dim3(nb), dim3(256), 0, p->stream, grad_energy, (const float*)src[i], (float*)dst[i], m[i]);
-  }
+  const int64_t m = 3 * (n_ion + n_wc);
+  if (m == 0) return DPLR_LR_OK;
+  const unsigned nb = (unsigned)((m + 255) / 256);
+  if (p->fp64)
+    hipLaunchKernelGGL(k_scale_grad<double>, dim3(nb), dim3(256), 0, p->stream, grad_energy, (const double*)ion_force,
+                       (double*)ion_grad, 3 * n_ion, (const double*)wc_force, (double*)wc_grad, 3 * n_wc);
+  else
+    hipLaunchKernelGGL(k_scale_grad<float>, dim3(nb), dim3(256), 0, p->stream, grad_energy, (const float*)ion_force,
+                       (float*)ion_grad, 3 * n_ion, (const float*)wc_force, (float*)wc_grad, 3 * n_wc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(p, e, "scale_grad launch");
   return DPLR_LR_OK;
@@ -1259,7 +1287,7 @@ dplr_lr_status dplr_lr_debug_copy(dplr_lr_plan p, int32_t which, void* dst, int6
     if (e != hipSuccess) return hip_fail(p, e, "debug copy");
     return DPLR_LR_OK;
   }
-  if (which == DPLR_LR_BUF_SPECTRUM && p->plane && p->geo.nsplit > 1) {
+  if (which == DPLR_LR_BUF_SPECTRUM && p->plane && p->last_split > 1) {
     // the plane spread leaves one partial spectrum per particle split: report their sum
     const size_t cs = 2 * p->tsize;
     if ((size_t)bytes % cs) return fail(p, DPLR_LR_E_INVALID, "size must be a whole number of complex values");
@@ -1268,10 +1296,10 @@ dplr_lr_status dplr_lr_debug_copy(dplr_lr_plan p, int32_t which, void* dst, int6
     if (n > 0) {
       if (p->fp64)
         hipLaunchKernelGGL(k_sum_partials<double>, dim3(nb), dim3(256), 0, p->stream, (cpx<double>*)dst,
-                           (const cpx<double>*)p->spec, p->geo.nsplit, nspec, n);
+                           (const cpx<double>*)p->spec, p->last_split, nspec, n);
       else
         hipLaunchKernelGGL(k_sum_partials<float>, dim3(nb), dim3(256), 0, p->stream, (cpx<float>*)dst,
-                           (const cpx<float>*)p->spec, p->geo.nsplit, nspec, n);
+                           (const cpx<float>*)p->spec, p->last_split, nspec, n);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(p, e, "debug copy");

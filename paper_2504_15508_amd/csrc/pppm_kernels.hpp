@@ -50,6 +50,7 @@ struct Geo {
   int nzblk;     // z-pass blocks
   int xyb;       // y rows per block of the inverse x pass
   int zgroup;    // z-pass column blocks per 128-byte output line (run on one XCD)
+  double invK[3];  // 1 / K (exact for powers of two)
 };
 
 struct PoissonConsts {
@@ -107,7 +108,7 @@ __device__ __forceinline__ void particle_bin(const T* __restrict__ ion_pos, cons
   for (int a = 0; a < 3; ++a) {
     const double K = (double)g.K[a];
     double v = (double)r[a] * invh[a];
-    v = v - K * floor(v / K);
+    v = v - K * floor(v * g.invK[a]);
     if (v >= K) v -= K;
     if (!(v >= 0.0 && v < K)) v = 0.0;  // also maps NaN/Inf inputs to 0
     const double av = v - 0.5 * P;
@@ -333,9 +334,16 @@ __device__ __forceinline__ int block_exclusive_scan(const int* __restrict__ v, i
   return wsum[16];
 }
 
+// At most this many chunks: the placement adds up the chunk histograms itself,
+// all of a bin's in flight together, instead of k_bin_colscan (a launch of
+// 3.4 us at 16,384 particles).
+constexpr int kPlaceScanChunks = 16;
+constexpr int kPlaceScanBins = 4096;  // and at most this many bins (4 a thread)
+
 // Placement.  Every block first turns the bin totals into bin starts (an
 // exclusive scan in LDS; block 0 also publishes them as bin_start), then
-// scatters its chunk.
+// scatters its chunk.  With at most kPlaceScanChunks chunks the totals and its
+// own offsets come from the raw histograms, otherwise from k_bin_colscan.
 template <typename T, int P>
 __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_pos, const T* __restrict__ wc_pos,
                                                     const T* __restrict__ ion_q, const T* __restrict__ wc_q,
@@ -349,25 +357,65 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
   int* start = lc + g.nbins;
   __shared__ unsigned qm;
   __shared__ int wsum[17];
-  for (int b = threadIdx.x; b < g.nbins; b += blockDim.x) lc[b] = 0;
   if (threadIdx.x == 0) qm = 0u;
-  const int all = block_exclusive_scan(total, start, g.nbins, wsum);  // contains barriers
+  constexpr int kOwn = kPlaceScanBins / 1024;
+  int own[kOwn];  // counts of the chunks before this one, bins threadIdx.x + 1024 u
+  const bool own_scan = (int)gridDim.x <= kPlaceScanChunks && g.nbins <= kPlaceScanBins;
+  if (own_scan) {
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int b = threadIdx.x + 1024 * u;
+      own[u] = 0;
+      if (b < g.nbins) {
+        int h[kPlaceScanChunks], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kPlaceScanChunks; ++k)
+          h[k] = hist[(size_t)min(k, (int)gridDim.x - 1) * g.nbins + b];
+#pragma unroll
+        for (int k = 0; k < kPlaceScanChunks; ++k) {
+          if (k < (int)blockIdx.x) own[u] += h[k];
+          if (k < (int)gridDim.x) sum += h[k];
+        }
+        lc[b] = sum;
+      }
+    }
+    __syncthreads();
+  }
+  const int all = own_scan ? block_exclusive_scan(lc, start, g.nbins, wsum)
+                           : block_exclusive_scan(total, start, g.nbins, wsum);  // contains barriers
   __syncthreads();
   if (blockIdx.x == 0) {
     for (int b = threadIdx.x; b < g.nbins; b += blockDim.x) bin_start[b] = start[b];
     if (threadIdx.x == 0) bin_start[g.nbins] = all;
+    __syncthreads();
   }
+  // this chunk's first slot of every bin, and its running count
+  if (own_scan) {
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int b = threadIdx.x + 1024 * u;
+      if (b < g.nbins) {
+        lc[b] = 0;
+        start[b] += own[u];
+      }
+    }
+  } else {
+    for (int b = threadIdx.x; b < g.nbins; b += blockDim.x) {
+      lc[b] = 0;
+      start[b] += hist[(size_t)blockIdx.x * g.nbins + b];
+    }
+  }
+  __syncthreads();
   unsigned qb = 0u;
   const double invh[3] = {ihx, ihy, ihz};
   const int64_t i0 = (int64_t)blockIdx.x * chunk;
   const int64_t i1 = min(n, i0 + chunk);
-  const int* off = hist + (size_t)blockIdx.x * g.nbins;
   for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
     T d[3];
     int sp, bin;
     particle_bin<T, P>(ion_pos, wc_pos, n_ion, i, invh, g, d, sp, bin);
     const T q = (i < n_ion) ? ion_q[i] : wc_q[i - n_ion];
-    const int slot = start[bin] + off[bin] + atomicAdd(lc + bin, 1);
+    const int slot = start[bin] + atomicAdd(lc + bin, 1);
     sorted[slot] = T4<T>{d[0], d[1], d[2], q};
     sidx[slot] = sp;
     perm[slot] = (int)i;
@@ -377,6 +425,62 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
   if ((threadIdx.x & 63) == 0) atomicMax(&qm, qb);
   __syncthreads();
   if (threadIdx.x == 0) qmax_part[blockIdx.x] = qm;
+}
+
+// The whole sort in one block, for particle counts where its launches are what
+// counts (hist, colscan and place take 2.0, 3.2 and 3.9 us for 256 particles).
+// A thread keeps its particles' records in registers between counting and
+// placing.  Above kSmallSort particles one compute unit's FP64 rate is the limit.
+constexpr int kSmallSort = 4096;
+template <typename T, int P>
+__global__ void __launch_bounds__(1024) k_sort_small(const T* __restrict__ ion_pos, const T* __restrict__ wc_pos,
+                                                     const T* __restrict__ ion_q, const T* __restrict__ wc_q,
+                                                     int64_t n_ion, int64_t n, double ihx, double ihy, double ihz,
+                                                     int* __restrict__ bin_start, T4<T>* __restrict__ sorted,
+                                                     int* __restrict__ sidx, int* __restrict__ perm,
+                                                     unsigned* __restrict__ qmax_part, Geo g) {
+  extern __shared__ int lc[];  // [nbins] counts, then [nbins] bin starts
+  int* start = lc + g.nbins;
+  __shared__ unsigned qm;
+  __shared__ int wsum[17];
+  for (int b = threadIdx.x; b < g.nbins; b += blockDim.x) lc[b] = 0;
+  if (threadIdx.x == 0) qm = 0u;
+  __syncthreads();
+  constexpr int U = kSmallSort / 1024;
+  const double invh[3] = {ihx, ihy, ihz};
+  T d[U][3], q[U];
+  int sp[U], bin[U], rank[U];
+  unsigned qb = 0u;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = (int64_t)u * 1024 + threadIdx.x;
+    if (i < n) {
+      particle_bin<T, P>(ion_pos, wc_pos, n_ion, i, invh, g, d[u], sp[u], bin[u]);
+      q[u] = (i < n_ion) ? ion_q[i] : wc_q[i - n_ion];
+      rank[u] = atomicAdd(lc + bin[u], 1);
+      qb = max(qb, abs_q_bits(q[u]));
+    }
+  }
+  qb = wave_max_u32(qb);
+  if ((threadIdx.x & 63) == 0) atomicMax(&qm, qb);
+  __syncthreads();
+  const int all = block_exclusive_scan(lc, start, g.nbins, wsum);  // contains barriers
+  __syncthreads();
+  for (int b = threadIdx.x; b < g.nbins; b += blockDim.x) bin_start[b] = start[b];
+  if (threadIdx.x == 0) {
+    bin_start[g.nbins] = all;
+    qmax_part[0] = qm;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = (int64_t)u * 1024 + threadIdx.x;
+    if (i < n) {
+      const int slot = start[bin[u]] + rank[u];
+      sorted[slot] = T4<T>{d[u][0], d[u][1], d[u][2], q[u]};
+      sidx[slot] = sp[u];
+      perm[slot] = (int)i;
+    }
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -1030,11 +1134,17 @@ __global__ void __launch_bounds__(kFftyThreads) k_ffty(cpx<T>* __restrict__ data
 //   component cancel in +-n pairs).
 //
 // The pass waits on memory: every value of a column is needed before its first
-// butterfly.  So all 16 loads of a partial spectrum are in flight together
-// (one round trip per partial; one per value and partial took 35 us instead of
-// 16 on a 32^3 mesh of 8 partials, 24.3 instead of 21.0 at 128^3 with 2), and
-// the influence values are loaded before the forward transform.
+// butterfly.  So many partial spectra are loaded by all threads (the register
+// transform would load with a third of them), many values at a time, and the
+// influence values before the forward transform.  (32^3, 8 partials: one round
+// trip per value and partial took 35 us, one per partial 16, this 11; 64^3: 37,
+// 15.5, 12.6.)
 // ----------------------------------------------------------------------------
+template <int N>
+struct IntC {
+  static constexpr int value = N;
+};
+
 template <typename T>
 __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict__ spec, int nsum, size_t sum_stride,
                                                        int nout, int bslot, cpx<T>* __restrict__ fspec,
@@ -1076,11 +1186,38 @@ __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict_
   // forward z transform of the yb columns, the partial spectra of the particle
   // splits added in split order on the way in
   copy_g2s<8>(tw, twg, g.twN);
+  load_G();
+  // the partial spectra of the particle splits (1, 2, 4 or 8 of them) are added
+  // in split order by all threads of the block, the loads of up to 16 values in
+  // flight together
+  auto stage = [&](auto count) {
+    constexpr int NS = decltype(count)::value, E = NS >= 8 ? 2 : NS >= 4 ? 4 : 8;  // elements at a time
+    for (int b = threadIdx.x; b < n; b += E * blockDim.x) {
+      cpx<T> r[E][NS];
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const int e = min(b + u * (int)blockDim.x, n - 1);
+        const cpx<T>* src = spec + col0 + imul(e >> lyb, Ky) + (e & (yb - 1));
+#pragma unroll
+        for (int sp = 0; sp < NS; ++sp) r[u][sp] = src[(size_t)sp * sum_stride];
+      }
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const int e = b + u * blockDim.x;
+        cpx<T> v = r[u][0];
+#pragma unroll
+        for (int sp = 1; sp < NS; ++sp) v = cadd(v, r[u][sp]);
+        if (e < n) buf[imul(e >> lyb, w2) + (e & (yb - 1))] = v;
+      }
+    }
+  };
+  // up to two partials: the register transform's threads load their own 16
+  // values a partial, without the way through LDS (20.6 against 21.2 us at 128^3)
   auto load_s = [&](cpx<T> (&v)[16], int yl, auto elem) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = spec[col0 + imul(elem(i), Ky) + yl];
-    for (int sp = 1; sp < nsum; ++sp) {
-      const cpx<T>* ps = spec + (size_t)sp * sum_stride;
+    if (nsum == 2) {
+      const cpx<T>* ps = spec + sum_stride;
       cpx<T> r[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) r[i] = ps[col0 + imul(elem(i), Ky) + yl];
@@ -1089,29 +1226,15 @@ __global__ void __launch_bounds__(1024) k_fftz_poisson(const cpx<T>* __restrict_
     }
   };
   auto store_b = [&](int yl, int z, const cpx<T>& v) { buf[imul(z, w2) + yl] = v; };
-  load_G();
-  if (!fft_cols_io<T, false>(buf, yb, Kz, w2, tw, g.twN, load_s, store_b)) {
-    cpx<T> r[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * blockDim.x;
-      if (e < n) r[u] = spec[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))];
-    }
-    // partial spectra of the other particle splits, added in split order
-    for (int sp = 1; sp < nsum; ++sp) {
-      const cpx<T>* ps = spec + (size_t)sp * sum_stride;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = threadIdx.x + u * blockDim.x;
-        if (e < n) r[u] = cadd(r[u], ps[col0 + imul(e >> lyb, Ky) + (e & (yb - 1))]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * blockDim.x;
-      if (e < n) buf[imul(e >> lyb, w2) + (e & (yb - 1))] = r[u];
+  if (nsum > 2 || !fft_cols_io<T, false>(buf, yb, Kz, w2, tw, g.twN, load_s, store_b)) {
+    switch (nsum) {
+      case 1: stage(IntC<1>{}); break;
+      case 2: stage(IntC<2>{}); break;
+      case 4: stage(IntC<4>{}); break;
+      default: stage(IntC<8>{}); break;
     }
     __syncthreads();
+    // forward z transform of the yb columns
     fft_rows<T, false, fft_ept<T>()>(buf, yb, Kz, 1, w2, true, tw, g.twN);
   }
 
@@ -1326,7 +1449,7 @@ __global__ void __launch_bounds__(512) k_ifftx(const cpx<T>* __restrict__ fspec,
 // differentiation).  Block b serves plane z = 8 (b / (8 ncomp)) + b % 8 and
 // component (b / 8) % ncomp, so the components of a plane land on the same XCD
 // (blocks are dealt round-robin over 8 XCDs): its L2 serves the second read of
-// A and merges the partial record writes.  Block 0 also performs the final
+// A and merges the partial record writes.  One more block performs the final
 // energy/virial reduction.
 // ----------------------------------------------------------------------------
 template <typename T>
@@ -1345,6 +1468,10 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
   const size_t b_ty = (size_t)KR * RY * sizeof(cpx<T>);
   const size_t b_tx = (size_t)(Ky / 2) * RS * sizeof(cpx<T>);
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem + max(b_ty, b_tx));
+  if ((int)blockIdx.x == ncomp * Kz) {  // the last block only reduces, beside the transforms
+    reduce_partials(partials, g.nzblk, pre, energy, virial, reinterpret_cast<double*>(smem));
+    return;
+  }
   const int zx = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int zg = slot / ncomp, a = slot - ncomp * zg;
   const int z = zg * 8 + zx;
@@ -1435,10 +1562,6 @@ __global__ void __launch_bounds__(1024) k_ifft_xy(const cpx<T>* __restrict__ fsp
   for (int e = threadIdx.x; e < imul(Ky, xpad); e += blockDim.x) {
     const int y = e / xpad, x = e - y * xpad;
     out[(size_t)(imul(y, RX) + Kx + x) * ncomp] = tr[2 * (imul(y >> 1, RS) + lds_pad(x)) + (y & 1)];
-  }
-  if (energy && blockIdx.x == 0) {
-    __syncthreads();
-    reduce_partials(partials, g.nzblk, pre, energy, virial, reinterpret_cast<double*>(smem));
   }
 }
 
@@ -1869,10 +1992,13 @@ __global__ void k_influence(double* __restrict__ G, Geo g, double Lx, double Ly,
 // Backward of E with respect to positions: grad = -g * F.
 // ----------------------------------------------------------------------------
 template <typename T>
-__global__ void k_scale_grad(const double* __restrict__ gE, const T* __restrict__ f, T* __restrict__ out, int64_t m) {
+__global__ void k_scale_grad(const double* __restrict__ gE, const T* f_ion, T* out_ion, int64_t m_ion, const T* f_wc,
+                             T* out_wc, int64_t m_wc) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  out[i] = (T)(-(*gE) * (double)f[i]);
+  if (i >= m_ion + m_wc) return;
+  const T* f = i < m_ion ? f_ion + i : f_wc + (i - m_ion);
+  T* out = i < m_ion ? out_ion + i : out_wc + (i - m_ion);
+  *out = (T)(-(*gE) * (double)*f);
 }
 
 }  // namespace dplr

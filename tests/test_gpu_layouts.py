@@ -100,3 +100,29 @@ def test_noalloc_shares_its_scratch(torch, mesh, order, precision):
         got = dl.plan.compute_noalloc(mesh, box, *x, order=order, beta=BETA, coulomb_k=KE)
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("mesh,order,precision", [((32, 16, 32), 5, "fp32"), ((16, 32, 16), 4, "fp64"),
+                                                  ((12, 18, 20), 3, "fp32")])
+@pytest.mark.parametrize("n", [2, 1024, 1025, 4096, 4097, 5121, 16384, 16385])
+def test_sort_forms(torch, mesh, order, precision, n):
+    """The one-block sort up to 4,096 particles, the placement that adds up the
+    chunk histograms up to 16 chunks of 1,024, the column scan beyond; the
+    spread's block sizes and (FP64) particle splits change along the way."""
+    import paper_2504_15508_amd as dl
+    box = np.array([9.0, 10.0, 9.5]) * np.array(mesh) / 16
+    pos, q = _gas(n, box, n)
+    plan = dl.Plan(mesh, order=order, beta=BETA, coulomb_k=KE, precision=precision, capacity=n)
+    plan.set_box(box)
+    E, F, W = _run(torch, plan, pos, q)
+    E0, F0, W0 = pppm.pppm(pos, q, box, mesh, order, BETA, KE)
+    assert np.linalg.norm(F - F0) <= BAR[precision] * np.linalg.norm(F0)
+    assert abs(E - E0) <= BAR[precision] * abs(E0)
+    assert np.abs(W - W0).max() <= BAR[precision] * abs(E0)
+    again = _run(torch, plan, pos, q)
+    assert again[0] == E and np.array_equal(again[1], F) and np.array_equal(again[2], W)
+    # fewer particles through the same buffers
+    k = max(1, n // 3)
+    Ek = _run(torch, plan, pos[:k], q[:k])[0]
+    E1 = pppm.pppm(pos[:k], q[:k], box, mesh, order, BETA, KE)[0]
+    assert abs(Ek - E1) <= BAR[precision] * abs(E1)
