@@ -13,8 +13,8 @@ import torch
 class DPLRLongRange(torch.autograd.Function):
     @staticmethod
     def forward(ctx, ion_pos, wc_pos, ion_q, wc_q, plan):
-        energy, f_ion, f_wc, virial = plan.compute(ion_pos.detach().contiguous(), ion_q.detach().contiguous(),
-                                                   wc_pos.detach().contiguous(), wc_q.detach().contiguous())
+        energy, f_ion, f_wc, virial = plan.compute(ion_pos.contiguous(), ion_q.contiguous(),
+                                                   wc_pos.contiguous(), wc_q.contiguous())
         plan.last_virial = virial
         ctx.plan = plan
         ctx.save_for_backward(f_ion, f_wc)

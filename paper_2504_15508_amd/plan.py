@@ -5,6 +5,7 @@ library's HIP kernels.  PyTorch provides device memory and the current HIP
 stream."""
 from __future__ import annotations
 
+import contextlib
 import ctypes
 from typing import Optional, Sequence
 
@@ -16,7 +17,21 @@ _DT = {"fp32": torch.float32, "fp64": torch.float64}
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else None
+    return t.data_ptr() if t is not None and t.numel() > 0 else None
+
+
+# A step of a few hundred particles takes the GPU 40 us, so the calls around it
+# count: the device is switched only when another one is current, and the
+# stream handle is read without building a Stream object.
+_current = contextlib.nullcontext()
+
+
+def _on(device: torch.device):
+    return _current if torch.cuda.current_device() == device.index else torch.cuda.device(device)
+
+
+def _stream(device: torch.device) -> int:
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
 
 
 class Plan:
@@ -73,11 +88,13 @@ class Plan:
 
     # -- plumbing ---------------------------------------------------------
     def _bind_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
-        _lib.check(_lib.load().dplr_lr_set_stream(self._h, ctypes.c_void_p(s)), self._h)
+        st = _lib.load().dplr_lr_set_stream(self._h, _stream(self.device))
+        if st:
+            _lib.check(st, self._h)
 
     def _check(self, st):
-        _lib.check(st, self._h)
+        if st:
+            _lib.check(st, self._h)
 
     @property
     def workspace_bytes(self) -> int:
@@ -125,12 +142,12 @@ class Plan:
             energy = torch.empty((), dtype=torch.float64, device=dev)
         if virial is None:
             virial = torch.empty(6, dtype=torch.float64, device=dev)
-        with torch.cuda.device(dev):
+        with _on(dev):
             self._bind_stream()
             self._check(_lib.load().dplr_lr_compute_energy_forces_virial(
                 self._h, n_ion, _ptr(ion_pos), _ptr(ion_q), n_wc, _ptr(wc_pos), _ptr(wc_q),
-                _ptr(ion_force), _ptr(wc_force), ctypes.c_void_p(energy.data_ptr()),
-                ctypes.c_void_p(virial.data_ptr())))
+                _ptr(ion_force), _ptr(wc_force), energy.data_ptr(),
+                virial.data_ptr()))
         return energy, ion_force, wc_force, virial
 
     def scale_grad(self, grad_energy, ion_force, wc_force, ion_grad=None, wc_grad=None):
@@ -141,10 +158,10 @@ class Plan:
             ion_grad = torch.empty_like(ion_force)
         if wc_grad is None:
             wc_grad = torch.empty_like(wc_force)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             self._bind_stream()
             self._check(_lib.load().dplr_lr_scale_grad(
-                self._h, ctypes.c_void_p(grad_energy.data_ptr()), ion_force.shape[0], _ptr(ion_force),
+                self._h, grad_energy.data_ptr(), ion_force.shape[0], _ptr(ion_force),
                 _ptr(ion_grad), wc_force.shape[0], _ptr(wc_force), _ptr(wc_grad)))
         return ion_grad, wc_grad
 
@@ -258,10 +275,8 @@ def compute_noalloc(mesh, box, ion_pos, ion_q, wc_pos=None, wc_q=None, order: in
     if virial is None:
         virial = torch.empty(6, dtype=torch.float64, device=dev)
     boxa = (ctypes.c_double * 3)(*[float(b) for b in box])
-    with torch.cuda.device(dev):
-        stream = torch.cuda.current_stream(dev).cuda_stream
+    with _on(dev):
         _lib.check(lib.dplr_lr_compute_noalloc(
             ctypes.byref(cfg), boxa, n_ion, _ptr(ion_pos), _ptr(ion_q), n_wc, _ptr(wc_pos), _ptr(wc_q),
-            _ptr(ion_force), _ptr(wc_force), ctypes.c_void_p(energy.data_ptr()),
-            ctypes.c_void_p(virial.data_ptr()), ctypes.c_void_p(stream)))
+            _ptr(ion_force), _ptr(wc_force), energy.data_ptr(), virial.data_ptr(), _stream(dev)))
     return energy, ion_force, wc_force, virial
