@@ -442,15 +442,31 @@ __global__ void __launch_bounds__(256) k_mixed_reduce(const double* __restrict__
 //    LDS; writes the real fields interleaved for the gather.
 // ---------------------------------------------------------------------------
 
-// Most points of a plane the fused kernels hold (128 KiB of complex values;
-// the bound also keeps a stage's butterflies within the registers of a
-// 1024-thread block).
+// Most points of a plane the fused kernels hold (128 KiB of complex values),
+// the threads for them and the points per thread, which bound a thread's
+// butterflies.  The stages are bound by instruction issue: a full FP32 plane
+// of 120 x 120 has 1,200 radix-12 butterflies, two for each of 640 threads or
+// more, and 768 threads leave the registers for them unspilled (1,024 spill
+// 28 bytes a lane; 48.0 and 48.8 us for the spread, 27.5 and 28.5 us for the
+// inverse pass).  FP64 takes 512: 768 spill.
 template <typename T>
 struct FusedPlane {
   static constexpr int kMaxPts = (128 * 1024) / (int)sizeof(cpx<T>);
+  static constexpr int kThreads = sizeof(T) == 8 ? 512 : 768;
+  static constexpr int kPer = (kMaxPts + kThreads - 1) / kThreads;
 };
 constexpr int kFusedZMaxPts = 2048;  // C Kz bound of k_mixed_fftz_poisson (one field)
-constexpr int kFusedZThreads = 512;
+constexpr int kFusedZThreads = 256;  // its most threads
+constexpr int kFusedZPer = kFusedZMaxPts / kFusedZThreads;  // points per thread, one field
+
+// Threads of a block of the fused kernels for pts points: one radix-10
+// butterfly each, a multiple of 64 in [least, most].  More threads only wait
+// at the barriers (12 x 18 planes in FP64: inverse pass 6.6 us with 256
+// threads, 8.7 with 1,024; the z pass of 120^3 with 256 and 512 threads
+// holds 5 blocks a compute unit either way).
+inline int fused_threads(size_t pts, int least, int most) {
+  return std::max(least, (int)std::min<size_t>((pts / 10 + 63) / 64 * 64, (size_t)most));
+}
 
 // floor(x / d) for 0 <= x, d < 2^23 from the float reciprocal inv = 1 / d:
 // the estimate is off by at most one either way and is corrected.
@@ -493,6 +509,26 @@ __device__ __forceinline__ void dft_radix(cpx<T>* u, const cpx<T>* __restrict__ 
     u[0] = cadd(u[0], sm);
     u[1] = cadd(m, t);
     u[2] = csub(m, t);
+  } else if constexpr (R == 5 && (INV || sizeof(T) == 8)) {
+    // cos and sin of 2 pi / 5 and 4 pi / 5 on the sums and differences of the
+    // pairs u1, u4 and u2, u3: 32 operations where the sum over the root table
+    // takes 96.  The FP32 forward transforms keep that sum, so that energy and
+    // virial stay the same to the last bit.
+    const T c1 = (T)0.30901699437494742410, c2 = (T)-0.80901699437494742410;
+    const T s1 = (T)0.95105651629515357212, s2 = (T)0.58778525229247312917;
+    const cpx<T> a = cadd(u[1], u[4]), b = cadd(u[2], u[3]);
+    const cpx<T> c = csub(u[1], u[4]), d = csub(u[2], u[3]);
+    const cpx<T> m1 = {u[0].x + c1 * a.x + c2 * b.x, u[0].y + c1 * a.y + c2 * b.y};
+    const cpx<T> m2 = {u[0].x + c2 * a.x + c1 * b.x, u[0].y + c2 * a.y + c1 * b.y};
+    const cpx<T> n1 = {s1 * c.x + s2 * d.x, s1 * c.y + s2 * d.y};
+    const cpx<T> n2 = {s2 * c.x - s1 * d.x, s2 * c.y - s1 * d.y};
+    const cpx<T> t1 = INV ? cpx<T>{-n1.y, n1.x} : cpx<T>{n1.y, -n1.x};
+    const cpx<T> t2 = INV ? cpx<T>{-n2.y, n2.x} : cpx<T>{n2.y, -n2.x};
+    u[0] = cadd(u[0], cadd(a, b));
+    u[1] = cadd(m1, t1);
+    u[4] = csub(m1, t1);
+    u[2] = cadd(m2, t2);
+    u[3] = csub(m2, t2);
   } else if constexpr (R == 5) {
     const int st = N / 5;
     cpx<T> w[5];
@@ -587,13 +623,13 @@ __device__ __forceinline__ void stage_inplace(cpx<T>* buf, int N, int nrows, int
 #pragma unroll
   for (int j = 0; j < MAXB; ++j) {
     if ((int)threadIdx.x + j * (int)blockDim.x < total) {
-      const int k = wk.i - qdiv(wk.i, p, invp) * p;
-      const cpx<T>* row = buf + wk.r * rs;
+      const cpx<T>* a0 = buf + wk.r * rs + wk.i * es;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        cpx<T> v = row[(wk.i + q * nb) * es];
-        if (q > 0 && k > 0) v = cmul(v, tw[q * k * tstep]);
-        u[j][q] = v;
+      for (int q = 0; q < R; ++q) u[j][q] = a0[q * (nb * es)];
+      if (p > 1) {  // the first stage has no twiddles
+        const int m = (wk.i - qdiv(wk.i, p, invp) * p) * tstep;
+#pragma unroll
+        for (int q = 1; q < R; ++q) u[j][q] = cmul(u[j][q], tw[q * m]);
       }
     }
     wk.next(nrows, nb, rfast);
@@ -603,12 +639,11 @@ __device__ __forceinline__ void stage_inplace(cpx<T>* buf, int N, int nrows, int
 #pragma unroll
   for (int j = 0; j < MAXB; ++j) {
     if ((int)threadIdx.x + j * (int)blockDim.x < total) {
-      const int k = wo.i - qdiv(wo.i, p, invp) * p;
-      const int jj = (wo.i - k) * R + k;
-      cpx<T>* row = buf + wo.r * rs;
+      const int k = p > 1 ? wo.i - qdiv(wo.i, p, invp) * p : 0;
+      cpx<T>* b0 = buf + wo.r * rs + ((wo.i - k) * R + k) * es;
       dft_radix<T, R, INV>(u[j], tw, N);
 #pragma unroll
-      for (int s2 = 0; s2 < R; ++s2) row[(jj + s2 * p) * es] = u[j][s2];
+      for (int s2 = 0; s2 < R; ++s2) b0[s2 * (p * es)] = u[j][s2];
     }
     wo.next(nrows, nb, rfast);
   }
@@ -617,15 +652,14 @@ __device__ __forceinline__ void stage_inplace(cpx<T>* buf, int N, int nrows, int
 
 // In-place unnormalised DFT of every row, X[k] = sum_n x[n] exp(-+2 pi i n k
 // / N) (INV: +), stages of radix 4, 2, 3, 5 in that order of preference; tw
-// holds the N roots of unity of that sign.  MAXPTS bounds nrows N and BLOCK
-// is the block size, so no thread has more than MAXPTS / (R BLOCK)
-// butterflies in a stage.
+// holds the N roots of unity of that sign.  nrows N <= PER blockDim.x, so no
+// thread has more than ceil(PER / R) butterflies in a stage.
 #ifndef DPLR_MIXED_MAX_RADIX
 #define DPLR_MIXED_MAX_RADIX 12
 #endif
 // Radix of the next stage for rem points still to split: the largest of 16,
 // 12, 10, 8, 6, 5, 4, 3, 2 (at most DPLR_MIXED_MAX_RADIX: radix 16 needs more
-// registers than a 1024-thread block has without spilling) that divides rem.
+// registers than a plane's block has without spilling) that divides rem.
 __device__ __forceinline__ int pick_radix(int rem) {
   constexpr int kR[9] = {16, 12, 10, 8, 6, 5, 4, 3, 2};
 #pragma unroll
@@ -634,7 +668,7 @@ __device__ __forceinline__ int pick_radix(int rem) {
   return rem;  // not reached for 2-3-5 sizes
 }
 
-template <typename T, int BLOCK, int MAXPTS, bool INV>
+template <typename T, int PER, bool INV>
 __device__ __forceinline__ void lds_dft_rows(cpx<T>* buf, int N, int nrows, int rs, int es, bool rfast,
                                              const cpx<T>* __restrict__ tw) {
   int p = 1, rem = N;
@@ -643,7 +677,7 @@ __device__ __forceinline__ void lds_dft_rows(cpx<T>* buf, int N, int nrows, int 
 #define DPLR_STAGE(RR)                                                                              \
   case RR:                                                                                          \
     if constexpr (RR <= DPLR_MIXED_MAX_RADIX)                                                       \
-      stage_inplace<T, RR, (MAXPTS / RR + BLOCK - 1) / BLOCK, INV>(buf, N, nrows, rs, es, rfast, p, tw); \
+      stage_inplace<T, RR, (PER + RR - 1) / RR, INV>(buf, N, nrows, rs, es, rfast, p, tw); \
     break;
     switch (R) {
       DPLR_STAGE(16) DPLR_STAGE(12) DPLR_STAGE(10) DPLR_STAGE(8) DPLR_STAGE(6) DPLR_STAGE(5) DPLR_STAGE(4)
@@ -663,15 +697,13 @@ __device__ __forceinline__ void lds_dft_rows(cpx<T>* buf, int N, int nrows, int 
 // the tuned spread, 2^(30 - e) for charges below 2^e (the largest charge from
 // the sort's per-chunk maxima), so each term converts in single precision
 // (FP64 plans: 2^40).  The integer plane becomes complex in place: every
-// thread holds its values in registers across a barrier.  Block of 1024
-// threads; LDS (Kx Ky + Kx + Ky) complex values.
+// thread holds its values in registers across a barrier.  LDS (Kx Ky + Kx + Ky) complex values.
 template <typename T, int P>
-__global__ void __launch_bounds__(1024) k_mixed_spread_xy(const T4<T>* __restrict__ rec,
+__global__ void __launch_bounds__(FusedPlane<T>::kThreads) k_mixed_spread_xy(const T4<T>* __restrict__ rec,
                                                           const int* __restrict__ spk,
                                                           const int* __restrict__ bin_start, Geo g,
                                                           const unsigned* __restrict__ qmax_part, int nqpart,
                                                           cpx<T>* __restrict__ part) {
-  constexpr int kMax = FusedPlane<T>::kMaxPts;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned long long* pl = reinterpret_cast<unsigned long long*>(smem);
   cpx<T>* cp = reinterpret_cast<cpx<T>*>(smem);
@@ -734,22 +766,22 @@ __global__ void __launch_bounds__(1024) k_mixed_spread_xy(const T4<T>* __restric
   }
   __syncthreads();
   const double inv_scale = 1.0 / (double)scale;
-  constexpr int KV = (kMax + 1023) / 1024;
+  constexpr int KV = FusedPlane<T>::kPer;
   long long held[KV];
 #pragma unroll
   for (int j = 0; j < KV; ++j) {
-    const int e = threadIdx.x + j * 1024;
+    const int e = threadIdx.x + j * (int)blockDim.x;
     held[j] = e < nxy ? (long long)pl[e] : 0;
   }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < KV; ++j) {
-    const int e = threadIdx.x + j * 1024;
+    const int e = threadIdx.x + j * (int)blockDim.x;
     if (e < nxy) cp[e] = cpx<T>{(T)((double)held[j] * inv_scale), (T)0};
   }
   __syncthreads();
-  lds_dft_rows<T, 1024, kMax, false>(cp, Kx, Ky, Kx, 1, false, twx);  // x rows
-  lds_dft_rows<T, 1024, kMax, false>(cp, Ky, Kx, 1, Kx, true, twy);   // y columns
+  lds_dft_rows<T, FusedPlane<T>::kPer, false>(cp, Kx, Ky, Kx, 1, false, twx);  // x rows
+  lds_dft_rows<T, FusedPlane<T>::kPer, false>(cp, Ky, Kx, 1, Kx, true, twy);   // y columns
   cpx<T>* out = part + ((int64_t)split * Kz + z) * nxy;
   for (int e = threadIdx.x; e < nxy; e += blockDim.x) out[e] = cp[e];
 }
@@ -783,7 +815,7 @@ __global__ void __launch_bounds__(kFusedZThreads) k_mixed_fftz_poisson(
     a[e * C2 + c] = v;
   }
   __syncthreads();
-  lds_dft_rows<T, kFusedZThreads, kFusedZMaxPts, false>(a, Kz, C, 1, C2, true, tw);
+  lds_dft_rows<T, kFusedZPer, false>(a, Kz, C, 1, C2, true, tw);
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
   const int K[3] = {Kx, Ky, Kz};
   // this thread's columns: c = t mod C is the same on every pass of the loop
@@ -826,7 +858,7 @@ __global__ void __launch_bounds__(kFusedZThreads) k_mixed_fftz_poisson(
   __syncthreads();
   for (int m = threadIdx.x; m < Kz; m += blockDim.x) tw[m] = unit_root<T>(m, Kz, +1);
   __syncthreads();
-  lds_dft_rows<T, kFusedZThreads, 2 * kFusedZMaxPts, true>(a, Kz, C2, 1, C2, true, tw);
+  lds_dft_rows<T, 2 * kFusedZPer, true>(a, Kz, C2, 1, C2, true, tw);
   for (int t = threadIdx.x; t < C2 * Kz; t += blockDim.x) {
     const int e = t >> (lc + 1), c = t & (C2 - 1);
     const int64_t gi = col0 + (c < C ? c : c - C) + (int64_t)e * nxy;
@@ -844,21 +876,20 @@ __global__ void __launch_bounds__(kFusedZThreads) k_mixed_fftz_poisson(
   __syncthreads();
   if (th < 7) {
     double v = 0.0;
-#pragma unroll
-    for (int w = 0; w < kFusedZThreads / 64; ++w) v += wred[th][w];
+    for (int w = 0; w < (int)blockDim.x / 64; ++w) v += wred[th][w];
     partials[(size_t)blockIdx.x * 8 + th] = v;
   }
 }
 
 // Block (z, f): the inverse y and x transforms of plane z of field f (0: Ex +
 // i Ey, 1: Ez) in LDS; writes packed[4 e + 0..1] = (Ex, Ey) or packed[4 e + 2]
-// = Ez for mesh index e.  Block of 1024 threads; LDS (Kx Ky + Kx + Ky)
-// complex values.
+// = Ez for mesh index e.  LDS (Kx Ky + Kx + Ky) complex values.  120^3 FP32:
+// 31.8 us with the root-table radix 5, a division and a twiddle test for
+// every butterfly of the first stage too, 28.4 us now (bound by instruction
+// issue; the z pass, likewise, 42 and 30 us).
 template <typename T>
-__global__ void __launch_bounds__(1024) k_mixed_ifft_xy(const cpx<T>* __restrict__ fxy,
-                                                        const cpx<T>* __restrict__ fz, int Kx, int Ky,
-                                                        T* __restrict__ packed) {
-  constexpr int kMax = FusedPlane<T>::kMaxPts;
+__global__ void __launch_bounds__(FusedPlane<T>::kThreads) k_mixed_ifft_xy(const cpx<T>* __restrict__ fxy,
+                                                        const cpx<T>* __restrict__ fz, int Kx, int Ky, T* __restrict__ packed) {
   extern __shared__ __align__(16) unsigned char smem[];
   cpx<T>* cp = reinterpret_cast<cpx<T>*>(smem);
   const int nxy = Kx * Ky;
@@ -871,8 +902,8 @@ __global__ void __launch_bounds__(1024) k_mixed_ifft_xy(const cpx<T>* __restrict
   for (int m = threadIdx.x; m < Kx; m += blockDim.x) twx[m] = unit_root<T>(m, Kx, +1);
   for (int m = threadIdx.x; m < Ky; m += blockDim.x) twy[m] = unit_root<T>(m, Ky, +1);
   __syncthreads();
-  lds_dft_rows<T, 1024, kMax, true>(cp, Ky, Kx, 1, Kx, true, twy);   // y columns
-  lds_dft_rows<T, 1024, kMax, true>(cp, Kx, Ky, Kx, 1, false, twx);  // x rows
+  lds_dft_rows<T, FusedPlane<T>::kPer, true>(cp, Ky, Kx, 1, Kx, true, twy);   // y columns
+  lds_dft_rows<T, FusedPlane<T>::kPer, true>(cp, Kx, Ky, Kx, 1, false, twx);  // x rows
   if (f == 0) {
     for (int e = threadIdx.x; e < nxy; e += blockDim.x)
       *reinterpret_cast<cpx<T>*>(packed + 4 * (base + e)) = cp[e];
@@ -911,7 +942,10 @@ __device__ __forceinline__ void mixed_gather_column(const T4<T>* __restrict__ Ef
   bspline_weights<T, P>(dz, wz);
   int gx = sx + tx;
   if (gx >= Kx) gx -= Kx;
-  constexpr int TZB = (P <= 5) ? P : ((P <= 6) ? 3 : 2);
+  // planes whose rows are loaded together: 15 records in flight (FP32), 10
+  // (FP64).  Without the barrier below the compiler sinks most loads to their
+  // uses (120^3 FP32: 33.3 us, this way 31.9; 12 x 18 x 12 FP64: 8.2 and 7.4)
+  constexpr int TZB = sizeof(T) == 8 ? (P <= 5 ? 2 : 1) : (P <= 5 ? 3 : 2);
 #pragma unroll
   for (int tz0 = 0; tz0 < P; tz0 += TZB) {
     T4<T> r[TZB][P];
@@ -929,6 +963,7 @@ __device__ __forceinline__ void mixed_gather_column(const T4<T>* __restrict__ Ef
         }
       }
     }
+    __builtin_amdgcn_sched_barrier(0);  // all loads of the planes are in flight before the first use
 #pragma unroll
     for (int dzb = 0; dzb < TZB; ++dzb) {
       if (tz0 + dzb < P) {

@@ -126,3 +126,38 @@ def test_sort_forms(torch, mesh, order, precision, n):
     Ek = _run(torch, plan, pos[:k], q[:k])[0]
     E1 = pppm.pppm(pos[:k], q[:k], box, mesh, order, BETA, KE)[0]
     assert abs(Ek - E1) <= BAR[precision] * abs(E1)
+
+
+@pytest.mark.parametrize("mesh,precision", [
+    ((5, 6, 5), "fp32"), ((50, 50, 6), "fp32"), ((54, 50, 6), "fp32"), ((25, 15, 400), "fp32"),
+    ((90, 90, 10), "fp32"), ((125, 125, 10), "fp32"), ((128, 125, 20), "fp32"),
+    ((5, 6, 5), "fp64"), ((50, 54, 6), "fp64"), ((75, 75, 15), "fp64"), ((90, 90, 10), "fp64"), ((25, 10, 500), "fp64")])
+def test_block_sizes_of_the_fused_planes(torch, mesh, precision):
+    """Mixed meshes from the smallest blocks of the plane and z kernels to the
+    largest (planes of 30 to 16,000 points, z rows of 5 to 500)."""
+    import paper_2504_15508_amd as dl
+    box = np.array([9.0, 10.0, 9.5]) * np.array(mesh) / 16
+    pos, q = _gas(900, box, mesh[0] + mesh[2])
+    plan = dl.Plan(mesh, order=5, beta=BETA, coulomb_k=KE, precision=precision, capacity=len(q))
+    plan.set_box(box)
+    E, F, W = _run(torch, plan, pos, q)
+    E0, F0, W0 = pppm.pppm(pos, q, box, mesh, 5, BETA, KE)
+    assert np.linalg.norm(F - F0) <= BAR[precision] * np.linalg.norm(F0)
+    assert abs(E - E0) <= BAR[precision] * abs(E0)
+    assert np.abs(W - W0).max() <= BAR[precision] * abs(E0)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_sort_with_many_bins(torch, precision):
+    """More bins than the placement adds up by itself (4,096): their totals are staged."""
+    import paper_2504_15508_amd as dl
+    mesh = (128, 256, 128)
+    box = np.array([9.0, 10.0, 9.5]) * np.array(mesh) / 16
+    pos, q = _gas(6000, box, 77)
+    plan = dl.Plan(mesh, order=4, beta=BETA, coulomb_k=KE, precision=precision, capacity=len(q))
+    plan.set_box(box)
+    E, F, W = _run(torch, plan, pos, q)
+    E0, F0, W0 = pppm.pppm(pos, q, box, mesh, 4, BETA, KE)
+    assert np.linalg.norm(F - F0) <= BAR[precision] * np.linalg.norm(F0)
+    assert abs(E - E0) <= BAR[precision] * abs(E0)
+    assert np.abs(W - W0).max() <= BAR[precision] * abs(E0)
