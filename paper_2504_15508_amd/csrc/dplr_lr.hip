@@ -172,7 +172,7 @@ struct dplr_lr_plan_s {
   int mblk = 0;               // ... blocks (and partials) of the ik multiply
   size_t lds_mplane = 0;      // ... LDS of the plane spread (0: the plane does not fit; global atomics)
   void* mrec = nullptr;       // ... per-particle stencil offsets and charge (plane spread)
-  int* mspk = nullptr;        // ... per-particle packed stencil starts (plane spread)
+  int2* mspk = nullptr;       // ... per-particle packed stencil starts and original index (plane spread)
   int msplit = 1;             // ... particle ranges per plane of the split plane spread (partials in mmesh)
   size_t mfused = 0;          // ... LDS of the fused plane kernels (0: the per-axis transforms)
   int mzc = 1;                // ... columns per block of the fused z pass
@@ -190,8 +190,7 @@ struct dplr_lr_plan_s {
   bool block_hist = false;    // bins fit in LDS: sort without global atomics
   int max_chunks = DPLR_SORT_CHUNKS;
   void* sorted = nullptr;
-  int* perm = nullptr;
-  int* sidx = nullptr;
+  int2* sidx = nullptr;  // packed stencil starts, original index
   void* spec = nullptr;
   void* fspec = nullptr;
   void* field = nullptr;   // real fields [Kz][Ky][Kx] x (Ex, Ey, Ez)
@@ -479,7 +478,7 @@ void set_lds_attrs(dplr_lr_plan p) {
 // Returns the number of charge-maximum words written.
 template <typename T, int P>
 int launch_sort(dplr_lr_plan p, const Geo& g, const T* ip, const T* iq, const T* wp, const T* wq, int64_t n_ion,
-                int64_t n, const double ih[3], T4<T>* sorted, int* sidx, const int stage[3]) {
+                int64_t n, const double ih[3], T4<T>* sorted, int2* sidx, const int stage[3]) {
   hipStream_t s = p->stream;
   const size_t lds = sizeof(int) * g.nbins;
   if (n == 0) {
@@ -490,7 +489,7 @@ int launch_sort(dplr_lr_plan p, const Geo& g, const T* ip, const T* iq, const T*
   if (n <= kSmallSort && g.nbins <= kSmallSortBins) {
     ProfScope ps(p, stage[2]);
     hipLaunchKernelGGL((k_sort_small<T, P>), dim3(1), dim3(1024), 2 * lds, s, ip, wp, iq, wq, n_ion, n, ih[0], ih[1],
-                       ih[2], p->bin_start, sorted, sidx, p->perm, p->qmax, g);
+                       ih[2], p->bin_start, sorted, sidx, p->qmax, g);
     return 1;
   }
   // chunk size: a multiple of DPLR_SORT_CHUNK_ALIGN, at most max_chunks chunks,
@@ -513,7 +512,7 @@ int launch_sort(dplr_lr_plan p, const Geo& g, const T* ip, const T* iq, const T*
   {
     ProfScope ps(p, stage[2]);
     hipLaunchKernelGGL((k_bin_place<T, P>), dim3(nblk), dim3(1024), 2 * lds, s, ip, wp, iq, wq, n_ion, n, ih[0],
-                       ih[1], ih[2], p->bin_hist, p->bin_count, p->bin_start, sorted, sidx, p->perm, p->qmax,
+                       ih[1], ih[2], p->bin_hist, p->bin_count, p->bin_start, sorted, sidx, p->qmax,
                        (int)chunk, g);
   }
   return nblk;
@@ -567,7 +566,7 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
       const int nb = (int)((n + 255) / 256);
       ProfScope ps(p, 2);
       hipLaunchKernelGGL((k_bin_scatter<T, P>), dim3(nb), dim3(256), 0, s, ip, wp, (const T*)ion_q, (const T*)wc_q,
-                         n_ion, n, ih[0], ih[1], ih[2], p->bin_cursor, sorted, p->sidx, p->perm, p->qmax, g);
+                         n_ion, n, ih[0], ih[1], ih[2], p->bin_cursor, sorted, p->sidx, p->qmax, g);
     }
   }
   if (p->plane) {
@@ -635,12 +634,12 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
         const int nch = (int)((n + 255) / 256);
         const int nb = (nch + kXcd - 1) / kXcd * kXcd;
         hipLaunchKernelGGL((k_gather_ad<T, P>), dim3(nb), dim3(256), 0, s, reinterpret_cast<const T*>(p->field),
-                           sorted, p->sidx, p->perm, (int)n, nch, (T*)ion_force, (T*)wc_force, n_ion,
+                           sorted, p->sidx, (int)n, nch, (T*)ion_force, (T*)wc_force, n_ion,
                            (T)(p->cfg.coulomb_k / V), (T)(g.K[0] / p->box[0]), (T)(g.K[1] / p->box[1]),
                            (T)(g.K[2] / p->box[2]), acc, kXcd, g);
       } else if (ad) {
         hipLaunchKernelGGL((k_gather_ad_lanes<T, P>), dim3(nblk), dim3(256), 0, s,
-                           reinterpret_cast<const T*>(p->field), sorted, p->sidx, p->perm, (int)n, nchunks,
+                           reinterpret_cast<const T*>(p->field), sorted, p->sidx, (int)n, nchunks,
                            (T*)ion_force, (T*)wc_force, n_ion, (T)(p->cfg.coulomb_k / V), (T)(g.K[0] / p->box[0]),
                            (T)(g.K[1] / p->box[1]), (T)(g.K[2] / p->box[2]), acc, kXcd, g);
       } else {
@@ -649,7 +648,7 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
         if (p->nzout == 2)
           for (int a = 0; a < 3; ++a) fs[a] *= pc.two_pi_over_L[a];
         hipLaunchKernelGGL((k_gather<T, P>), dim3(nblk), dim3(256), 0, s, reinterpret_cast<const T*>(p->field),
-                           sorted, p->sidx, p->perm, (int)n, nchunks, (T*)ion_force, (T*)wc_force, n_ion,
+                           sorted, p->sidx, (int)n, nchunks, (T*)ion_force, (T*)wc_force, n_ion,
                            (T)fs[0], (T)fs[1], (T)fs[2], acc, kXcd, g);
       }
     }
@@ -736,11 +735,11 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
                                          n_ion, n, ih, (T4<T>*)p->mrec, p->mspk, stage);
     if (fused)
       hipLaunchKernelGGL((k_mixed_spread_xy<T, P>), dim3(g.K[2], S), dim3(plane_thr), p->mfused, s,
-                         (const T4<T>*)p->mrec, (const int*)p->mspk, (const int*)p->bin_start, gs,
+                         (const T4<T>*)p->mrec, (const int2*)p->mspk, (const int*)p->bin_start, gs,
                          (const unsigned*)p->qmax, nqpart, reinterpret_cast<cpx<T>*>(p->mmesh));
     else
       hipLaunchKernelGGL((k_mixed_spread_sorted<T, P>), dim3(g.K[2], S), dim3(1024), p->lds_mplane, s,
-                         (const T4<T>*)p->mrec, (const int*)p->mspk, (const int*)p->bin_start, gs, spec, p->mmesh);
+                         (const T4<T>*)p->mrec, (const int2*)p->mspk, (const int*)p->bin_start, gs, spec, p->mmesh);
     if (S > 1 && !fused)
       hipLaunchKernelGGL(k_mixed_combine<T>, dim3((unsigned)((ntot + 255) / 256)), dim3(256), 0, s,
                          (const long long*)p->mmesh, S, ntot, spec);
@@ -796,7 +795,7 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
     ProfScope ps(p, 15);
     if (p->lds_mplane)  // the sorted records of the spread
       hipLaunchKernelGGL((k_mixed_gather_sorted<T, P>), dim3(nbg), dim3(256), 0, s, (const T4<T>*)p->mrec,
-                         (const int*)p->mspk, (const int*)p->perm, n_ion, n, g.K[0], g.K[1], g.K[2],
+                         (const int2*)p->mspk, n_ion, n, g.K[0], g.K[1], g.K[2],
                          (const T4<T>*)p->mpacked, (T*)ion_force, (T*)wc_force,
                          q32 ? (T)1 : (T)(p->cfg.coulomb_k / V), (p->cfg.flags & DPLR_LR_ACCUMULATE) ? 1 : 0,
                          (const double*)p->partials, npart, p->cfg.coulomb_k / (2.0 * V), energy,
@@ -869,8 +868,8 @@ dplr_lr_status carve_workspace(dplr_lr_plan p, size_t cap, bool share, Get&& get
   const size_t b_hist = p->block_hist ? sizeof(int) * (size_t)p->max_chunks * g.nbins : 0;
   if (b_hist && !share) DPLR_ALLOC(p->bin_hist, b_hist, "bin histograms");
   DPLR_ALLOC(p->sorted, 4 * ts * cap, "sorted");
-  DPLR_ALLOC(p->perm, sizeof(int) * cap, "perm");
-  DPLR_ALLOC(p->sidx, sizeof(int) * cap, "stencil starts");
+  // two arrays' worth: a workspace of a fixed size takes the same systems as with two arrays of int
+  DPLR_ALLOC(p->sidx, 2 * ((sizeof(int) * cap + 255) & ~(size_t)255), "stencil starts and indices");
   // one partial charge spectrum per particle split; A and B of the inverse z
   // transform, or (separate inverse y and x passes) three field spectra; three
   // field components in rows padded by P - 1 records, or (analytic
@@ -1054,10 +1053,9 @@ dplr_lr_status dplr_lr_plan_create(const dplr_lr_config* cfg, void* hip_stream, 
       void* t2 = nullptr;
       dplr_lr_status sr = DPLR_LR_OK;
       if (p->lds_mplane) sr = alloc(p, &p->mrec, 4 * ts * capn, "mixed-radix stencil records");
-      if (p->lds_mplane && sr == DPLR_LR_OK) { sr = alloc(p, &t2, sizeof(int) * capn, "mixed-radix stencil starts"); p->mspk = (int*)t2; }
+      if (p->lds_mplane && sr == DPLR_LR_OK) { sr = alloc(p, &t2, sizeof(int2) * capn, "mixed-radix stencil starts and indices"); p->mspk = (int2*)t2; }
       // the counting sort's buffers (bins of every split count up to msplit)
       const size_t nb1 = (size_t)p->geo.nbins + 1;
-      if (p->lds_mplane && sr == DPLR_LR_OK) { sr = alloc(p, &t2, sizeof(int) * capn, "perm"); p->perm = (int*)t2; }
       if (p->lds_mplane && sr == DPLR_LR_OK) { sr = alloc(p, &t2, sizeof(int) * nb1, "bin_count"); p->bin_count = (int*)t2; }
       if (p->lds_mplane && sr == DPLR_LR_OK) { sr = alloc(p, &t2, sizeof(int) * nb1, "bin_start"); p->bin_start = (int*)t2; }
       if (p->lds_mplane && sr == DPLR_LR_OK) {

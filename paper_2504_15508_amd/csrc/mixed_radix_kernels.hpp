@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256) k_mixed_spread(const T* __restrict__ ion_
 // k_mixed_combine adds.  LDS Kx Ky 64-bit words.
 template <typename T, int P>
 __global__ void __launch_bounds__(1024) k_mixed_spread_sorted(const T4<T>* __restrict__ rec,
-                                                              const int* __restrict__ spk,
+                                                              const int2* __restrict__ spk,
                                                               const int* __restrict__ bin_start, Geo g,
                                                               cpx<T>* __restrict__ spec,
                                                               long long* __restrict__ partial) {
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(1024) k_mixed_spread_sorted(const T4<T>* __res
   for (int v = threadIdx.x; v < total; v += blockDim.x) {
     const int j = range_index2(R, v);
     const T4<T> rc = rec[j];
-    const int pk = spk[j];
+    const int pk = spk[j].x;
     const int sx = pk & 1023, sy = (pk >> 10) & 1023;
     int tz = z - (pk >> 20);
     if (tz < 0) tz += Kz;
@@ -700,7 +700,7 @@ __device__ __forceinline__ void lds_dft_rows(cpx<T>* buf, int N, int nrows, int 
 // thread holds its values in registers across a barrier.  LDS (Kx Ky + Kx + Ky) complex values.
 template <typename T, int P>
 __global__ void __launch_bounds__(FusedPlane<T>::kThreads) k_mixed_spread_xy(const T4<T>* __restrict__ rec,
-                                                          const int* __restrict__ spk,
+                                                          const int2* __restrict__ spk,
                                                           const int* __restrict__ bin_start, Geo g,
                                                           const unsigned* __restrict__ qmax_part, int nqpart,
                                                           cpx<T>* __restrict__ part) {
@@ -736,7 +736,7 @@ __global__ void __launch_bounds__(FusedPlane<T>::kThreads) k_mixed_spread_xy(con
   for (int v = threadIdx.x; v < total; v += blockDim.x) {
     const int j = range_index2(R, v);
     const T4<T> rc = rec[j];
-    const int pk = spk[j];
+    const int pk = spk[j].x;
     const int sx = pk & 1023, sy = (pk >> 10) & 1023;
     int tz = z - (pk >> 20);
     if (tz < 0) tz += Kz;
@@ -1006,11 +1006,10 @@ template <int P>
 constexpr int mixed_gather_per_block() { return 4 * (64 / P); }
 
 // From the sorted records of the plane spread: particle v of the sorted
-// order, force to the caller's index perm[v].
+// order, force to the caller's index spk[v].y.
 template <typename T, int P>
 __global__ void __launch_bounds__(256) k_mixed_gather_sorted(const T4<T>* __restrict__ rec,
-                                                             const int* __restrict__ spk,
-                                                             const int* __restrict__ perm, int64_t n_ion, int64_t n,
+                                                             const int2* __restrict__ spk, int64_t n_ion, int64_t n,
                                                              int Kx, int Ky, int Kz, const T4<T>* __restrict__ Ef,
                                                              T* __restrict__ ion_f, T* __restrict__ wc_f, T fscale,
                                                              int accumulate, const double* __restrict__ partials,
@@ -1031,8 +1030,9 @@ __global__ void __launch_bounds__(256) k_mixed_gather_sorted(const T4<T>* __rest
   int64_t src = 0;
   if (on) {
     const T4<T> rc = rec[v];
-    const int pk = spk[v];
-    src = perm[v];
+    const int2 sk = spk[v];
+    const int pk = sk.x;
+    src = sk.y;
     T wxt, dxt;
     bspline_weight_at<T, P>(rc.x, tx, wxt, dxt);
     mixed_gather_column<T, P>(Ef, Kx, Ky, Kz, pk & 1023, (pk >> 10) & 1023, pk >> 20, rc.y, rc.z, tx, part);

@@ -2,8 +2,11 @@
 //
 // Data layout in HBM (FP32 plan; FP64 doubles every element):
 //   sorted   [n] T4 (d_x, d_y, d_z, q): fractional B-spline offsets and charge,
-//            ordered by bin; sidx [n] int: stencil starts s_x | s_y<<10 | s_z<<20;
-//            perm [n] int: original index (ions 0..n_ion-1, then WCs).
+//            ordered by bin; sidx [n] int2: stencil starts s_x | s_y<<10 |
+//            s_z<<20 and original index (ions 0..n_ion-1, then WCs).  One
+//            8-byte store, because the sort's scattered stores write a
+//            partial line each (placement at 256^3, 1.2 M particles: 69 us
+//            with two arrays of int, 58 with one; at 128^3 10.6 and 9.5).
 //   bins     one per (split, stencil-start plane s_z, stencil-start row group
 //            s_y >> qshift), in that order of significance; bin_start
 //            [nbins+1].  The split is s_x / xs for pencil tiles and the
@@ -211,7 +214,7 @@ __global__ void __launch_bounds__(256) k_bin_scatter(const T* __restrict__ ion_p
                                                      const T* __restrict__ ion_q, const T* __restrict__ wc_q,
                                                      int64_t n_ion, int64_t n, double ihx, double ihy, double ihz,
                                                      int* __restrict__ cursor, T4<T>* __restrict__ sorted,
-                                                     int* __restrict__ sidx, int* __restrict__ perm,
+                                                     int2* __restrict__ sidx,
                                                      unsigned* __restrict__ qmax_bits, Geo g) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   unsigned qb = 0u;
@@ -223,8 +226,7 @@ __global__ void __launch_bounds__(256) k_bin_scatter(const T* __restrict__ ion_p
     const T q = (i < n_ion) ? ion_q[i] : wc_q[i - n_ion];
     const int slot = atomicAdd(cursor + bin, 1);
     sorted[slot] = T4<T>{d[0], d[1], d[2], q};
-    sidx[slot] = sp;
-    perm[slot] = (int)i;
+    sidx[slot] = make_int2(sp, (int)i);
     qb = abs_q_bits(q);
   }
   qb = wave_max_u32(qb);
@@ -351,8 +353,7 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
                                                     int64_t n_ion, int64_t n, double ihx, double ihy, double ihz,
                                                     const int* __restrict__ hist, const int* __restrict__ total,
                                                     int* __restrict__ bin_start,
-                                                    T4<T>* __restrict__ sorted, int* __restrict__ sidx,
-                                                    int* __restrict__ perm, unsigned* __restrict__ qmax_part,
+                                                    T4<T>* __restrict__ sorted, int2* __restrict__ sidx, unsigned* __restrict__ qmax_part,
                                                     int chunk, Geo g) {
   extern __shared__ int lc[];  // [nbins] ranks, then [nbins] bin starts
   int* start = lc + g.nbins;
@@ -386,7 +387,8 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
   if (staged) {
     // many totals go to LDS first, coalesced: a thread's stretch of them read
     // straight from memory is one line per load (16,384 bins of a 256^3 mesh:
-    // placement 78 us, this way 69; with 1,920 bins no gain)
+    // placement 78 us, this way 69, with one store for start and index
+    // below 58; with 1,920 bins no gain)
     copy_g2s<8>(start, total, g.nbins);
     __syncthreads();
   }
@@ -427,8 +429,7 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
     const T q = (i < n_ion) ? ion_q[i] : wc_q[i - n_ion];
     const int slot = start[bin] + atomicAdd(lc + bin, 1);
     sorted[slot] = T4<T>{d[0], d[1], d[2], q};
-    sidx[slot] = sp;
-    perm[slot] = (int)i;
+    sidx[slot] = make_int2(sp, (int)i);
     qb = max(qb, abs_q_bits(q));
   }
   qb = wave_max_u32(qb);
@@ -447,7 +448,7 @@ __global__ void __launch_bounds__(1024) k_sort_small(const T* __restrict__ ion_p
                                                      const T* __restrict__ ion_q, const T* __restrict__ wc_q,
                                                      int64_t n_ion, int64_t n, double ihx, double ihy, double ihz,
                                                      int* __restrict__ bin_start, T4<T>* __restrict__ sorted,
-                                                     int* __restrict__ sidx, int* __restrict__ perm,
+                                                     int2* __restrict__ sidx,
                                                      unsigned* __restrict__ qmax_part, Geo g) {
   extern __shared__ int lc[];  // [nbins] counts, then [nbins] bin starts
   int* start = lc + g.nbins;
@@ -487,8 +488,7 @@ __global__ void __launch_bounds__(1024) k_sort_small(const T* __restrict__ ion_p
     if (i < n) {
       const int slot = start[bin[u]] + rank[u];
       sorted[slot] = T4<T>{d[u][0], d[u][1], d[u][2], q[u]};
-      sidx[slot] = sp[u];
-      perm[slot] = (int)i;
+      sidx[slot] = make_int2(sp[u], (int)i);
     }
   }
 }
@@ -646,7 +646,7 @@ __device__ __forceinline__ long long to_fixed(T c) {
 // ----------------------------------------------------------------------------
 template <typename T, int P>
 __global__ void __launch_bounds__(512) k_spread_fftx(const T4<T>* __restrict__ sorted,
-                                                     const int* __restrict__ sidx,
+                                                     const int2* __restrict__ sidx,
                                                      const int* __restrict__ bin_start,
                                                      const unsigned* __restrict__ qmax_part, int nqpart,
                                                      cpx<T>* __restrict__ spec, size_t split_stride,
@@ -706,7 +706,7 @@ __global__ void __launch_bounds__(512) k_spread_fftx(const T4<T>* __restrict__ s
       if (v < total) {
         const int idx = range_index(R, v);
         pts[u] = sorted[idx];
-        sps[u] = sidx[idx];
+        sps[u] = sidx[idx].x;
       }
     }
 #pragma unroll
@@ -821,7 +821,7 @@ __global__ void __launch_bounds__(512) k_spread_fftx(const T4<T>* __restrict__ s
 // ----------------------------------------------------------------------------
 template <typename T, int P>
 __global__ void __launch_bounds__(1024) k_spread_xy(const T4<T>* __restrict__ sorted,
-                                                    const int* __restrict__ sidx,
+                                                    const int2* __restrict__ sidx,
                                                     const int* __restrict__ bin_start,
                                                     const unsigned* __restrict__ qmax_part, int nqpart,
                                                     cpx<T>* __restrict__ spec, size_t split_stride,
@@ -878,7 +878,7 @@ __global__ void __launch_bounds__(1024) k_spread_xy(const T4<T>* __restrict__ so
       if (v < total) {
         const int idx = range_index2(R, v);  // the P planes below z: at most two ranges
         pts[u] = sorted[idx];
-        sps[u] = sidx[idx];
+        sps[u] = sidx[idx].x;
       }
     }
 #pragma unroll
@@ -1701,7 +1701,7 @@ __device__ __forceinline__ void gather_field(const T* __restrict__ field, int RX
 // fx, fy, fz: k_e / V, times 2 pi / L_a where the spectra carry integer indices.
 template <typename T, int P>
 __global__ void __launch_bounds__(256) k_gather(const T* __restrict__ field, const T4<T>* __restrict__ sorted,
-                                                const int* __restrict__ sidx, const int* __restrict__ perm,
+                                                const int2* __restrict__ sidx,
                                                 int n, int nchunks, T* __restrict__ ion_f, T* __restrict__ wc_f,
                                                 int64_t n_ion, T fx, T fy, T fz, int accumulate, int nxcd, Geo g) {
   typedef GatherSplit<T, P> S;
@@ -1719,8 +1719,9 @@ __global__ void __launch_bounds__(256) k_gather(const T* __restrict__ field, con
   int sp = 0, src = 0;
   if (on) {
     pt = sorted[v];
-    sp = sidx[v];
-    src = perm[v];
+    const int2 si = sidx[v];
+    sp = si.x;
+    src = si.y;
   }
   T tot[3];
   gather_field<T, P>(field, g.K[0] + P - 1, g.K[1], g.K[2], sp & 1023, (sp >> 10) & 1023, sp >> 20, pt.x, pt.y, pt.z,
@@ -1753,7 +1754,7 @@ struct __attribute__((aligned(16))) Chunk16 {
 
 template <typename T, int P>
 __global__ void __launch_bounds__(256) k_gather_ad(const T* __restrict__ phi, const T4<T>* __restrict__ sorted,
-                                                   const int* __restrict__ sidx, const int* __restrict__ perm,
+                                                   const int2* __restrict__ sidx,
                                                    int n, int nchunks, T* __restrict__ ion_f, T* __restrict__ wc_f,
                                                    int64_t n_ion, T fscale, T ihx, T ihy, T ihz, int accumulate,
                                                    int nxcd, Geo g) {
@@ -1768,8 +1769,8 @@ __global__ void __launch_bounds__(256) k_gather_ad(const T* __restrict__ phi, co
   const int v = chunk * blockDim.x + threadIdx.x;
   if (chunk >= nchunks || v >= n) return;
   const T4<T> pt = sorted[v];
-  const int sp = sidx[v];
-  const int src = perm[v];
+  const int2 si = sidx[v];
+  const int sp = si.x, src = si.y;
   const int sx = sp & 1023, sy = (sp >> 10) & 1023, sz = sp >> 20;
   T wy[P], wz[P], dy[P], dz[P];
   bspline_weights<T, P>(pt.y, wy);
@@ -1854,7 +1855,7 @@ __global__ void __launch_bounds__(256) k_gather_ad(const T* __restrict__ phi, co
 // ----------------------------------------------------------------------------
 template <typename T, int P>
 __global__ void __launch_bounds__(256) k_gather_ad_lanes(const T* __restrict__ phi, const T4<T>* __restrict__ sorted,
-                                                   const int* __restrict__ sidx, const int* __restrict__ perm,
+                                                   const int2* __restrict__ sidx,
                                                    int n, int nchunks, T* __restrict__ ion_f, T* __restrict__ wc_f,
                                                    int64_t n_ion, T fscale, T ihx, T ihy, T ihz, int accumulate,
                                                    int nxcd, Geo g) {
@@ -1873,8 +1874,9 @@ __global__ void __launch_bounds__(256) k_gather_ad_lanes(const T* __restrict__ p
   int src = 0;
   if (on) {
     const T4<T> pt = sorted[v];
-    const int sp = sidx[v];
-    src = perm[v];
+    const int2 si = sidx[v];
+    const int sp = si.x;
+    src = si.y;
     const int sx = sp & 1023, sy = (sp >> 10) & 1023, sz = sp >> 20;
     T wy[P], wz[P], dy[P], dz[P], wxt, dxt;
     bspline_weight_at<T, P>(pt.x, tx, wxt, dxt);  // this lane's column only
