@@ -13,6 +13,7 @@
 //   mu[128] inv_sigma[128]                                   (18912 floats)
 #pragma once
 
+#include "cell_walk.hpp"
 #include "pppm_kernels.hpp"
 
 namespace dplr {
@@ -358,15 +359,10 @@ __global__ void __launch_bounds__(128) k_norm_finish(double* __restrict__ acc, f
 // Matrix instructions ignore the execution mask, so all loops are uniform over
 // the wave and a particle that is done contributes w = 0.
 // ---------------------------------------------------------------------------
-constexpr int kDescLanes = 4;
 constexpr int kDescThreads = 64;
 constexpr int kDescParts = kDescThreads / kDescLanes;
 constexpr int kNbrMax = 64;
-// candidates per lane in flight together (16 per particle and chunk; 8 a lane
-// need more registers than four waves a SIMD leave)
-constexpr int kScan = 4;
-constexpr int kScanPad = kScan * kDescLanes;  // spare entries behind the sorted particles
-static_assert(kScan * kDescLanes <= 32 && kNbrMax % kDescLanes == 0, "one word of candidate bits per chunk");
+static_assert(kScanChunk <= 32 && kNbrMax % kDescLanes == 0, "one word of candidate bits per chunk");
 
 // Pairs per round of the accumulation: every lane of a particle forms one
 // pair's quantities (once per pair), and then every lane runs its eight orders
@@ -496,54 +492,33 @@ __device__ __forceinline__ void descriptor_row(float (&T)[4], const f32x4& acc, 
 __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, int g,
                                                const float4* __restrict__ cpos, const int* __restrict__ start,
                                                const CellGeo& c, int base, int* list) {
-  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
-  const int cx = min((int)(pi.x * c.cinv[0]), nx - 1);
-  const int cy = min((int)(pi.y * c.cinv[1]), ny - 1);
-  const int cz = min((int)(pi.z * c.cinv[2]), nz - 1);
   const float rc2 = c.rc * c.rc;
-  // A row's cells cx-1, cx, cx+1 are consecutive; at the ends of the row they are
-  // two ranges (cells nx-1 | 0, 1 or nx-2, nx-1 | 0).  Segment q of the scan: row
-  // q / 2 (z outer, y inner), its first or second range.  Cells before 0 or past
-  // the end are one box length away.
-  auto segment = [&](int q, int& j0, int& j1) {
-    const int k = q >> 1, kz = (k * 11) >> 5, ky = k - 3 * kz;  // k / 3 for k < 9
-    const int y = cy + ky - 1, z = cz + kz - 1;
-    const int* row = start + ((z < 0 ? nz - 1 : z >= nz ? 0 : z) * ny + (y < 0 ? ny - 1 : y >= ny ? 0 : y)) * nx;
-    if (q & 1) {
-      j0 = row[0];
-      j1 = row[cx == 0 ? 2 : cx == nx - 1 ? 1 : 0];
-    } else {
-      j0 = row[cx == 0 ? nx - 1 : cx - 1];
-      j1 = row[cx == 0 ? nx : min(cx + 2, nx)];
-    }
-    if (!on) j1 = j0;
-  };
+  CellWalk w{start, c.nc[0], c.nc[1], c.nc[2], min((int)(pi.x * c.cinv[0]), c.nc[0] - 1),
+             min((int)(pi.y * c.cinv[1]), c.nc[1] - 1), min((int)(pi.z * c.cinv[2]), c.nc[2] - 1), on, 0, 0, 0, 0};
+  // cells before 0 or past the end are one box length away
   auto shifts = [&](int q, float& sx, float& sy, float& sz) {
-    const int k = q >> 1, kz = (k * 11) >> 5, ky = k - 3 * kz;
-    const int y = cy + ky - 1, z = cz + kz - 1;
-    sx = q & 1 ? (cx == nx - 1 ? -c.L[0] : 0.0f) : (cx == 0 ? c.L[0] : 0.0f);
-    sy = y < 0 ? c.L[1] : y >= ny ? -c.L[1] : 0.0f;
-    sz = z < 0 ? c.L[2] : z >= nz ? -c.L[2] : 0.0f;
+    const int y = w.row_y(q), z = w.row_z(q);
+    sx = q & 1 ? (w.cx == w.nx - 1 ? -c.L[0] : 0.0f) : (w.cx == 0 ? c.L[0] : 0.0f);
+    sy = y < 0 ? c.L[1] : y >= w.ny ? -c.L[1] : 0.0f;
+    sz = z < 0 ? c.L[2] : z >= w.nz ? -c.L[2] : 0.0f;
   };
-  const int dq = __any(cx == 0 || cx == nx - 1) ? 1 : 2;  // second ranges only where a particle of the wave has one
+  const int dq = __any(w.at_end()) ? 1 : 2;  // second ranges only where a particle of the wave has one
   int cnt = 0, q = 0;
-  int j0, j1, j0n, j1n;
   float sx, sy, sz;
-  segment(0, j0, j1);
+  w.begin(dq);
   shifts(0, sx, sy, sz);
-  segment(dq, j0n, j1n);  // bounds are loaded one segment ahead
-  // candidates j0 + 4 u + g, u < kScan, of the next chunk (past the range or the
-  // array's end: masked below; the array has kScanPad spare entries)
+  // candidates j0 + 4 u + g, u < kScan, of the next chunk (those past the range are
+  // masked below; the array has kScanPad spare entries for the last range's)
   float3 pj[kScan];
   auto fetch = [&]() {
-    const float4* src = cpos + j0 + g;
+    const float4* src = cpos + w.j0 + g;
 #pragma unroll
     for (int u = 0; u < kScan; ++u) pj[u] = *reinterpret_cast<const float3*>(src + kDescLanes * u);
   };
   fetch();
-  while (q < 18) {
-    const int jc = j0 + g;
-    const int left = min(max(j1 - j0, 0), kScan * kDescLanes);
+  while (q < kSegments) {
+    const int jc = w.j0 + g;
+    const int left = w.left();
     // bit 4 u + g of the particle's word: candidate 4 u + g is inside the cutoff
     // (and not at the particle's own place: not itself)
     unsigned bits = 0u;
@@ -559,13 +534,11 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
       for (int u = 0; u < kScan; ++u) test(u, pj[u].x - pi.x, pj[u].y - pi.y, pj[u].z - pi.z);
     }
     // the next chunk's candidates arrive while this one's are listed
-    j0 += kScan * kDescLanes;
-    if (!__any(j0 < j1)) {
+    w.advance();
+    if (!__any(w.j0 < w.j1)) {
       q += dq;
-      j0 = j0n;
-      j1 = j1n;
-      shifts(min(q, 17), sx, sy, sz);
-      segment(min(q + dq, 17), j0n, j1n);
+      w.next_segment(q + dq);
+      shifts(min(q, kSegments - 1), sx, sy, sz);
     }
     fetch();
     bits <<= g;
