@@ -40,6 +40,7 @@ void set_global_error(const char* m) { set_msg(g_global_error, m); }
 #ifndef DPLR_SPREAD_MAX_SPLIT
 #define DPLR_SPREAD_MAX_SPLIT 8
 #endif
+static_assert(DPLR_SPREAD_MAX_SPLIT <= 8, "k_fftz_poisson adds 1, 2, 4 or 8 partial spectra");
 // particle chunks of the counting sort (one LDS histogram each) and the
 // granularity of the chunk length; the per-bin chunk scan handles at most
 // 16 x 16 chunks
@@ -492,12 +493,7 @@ int launch_sort(dplr_lr_plan p, const Geo& g, const T* ip, const T* iq, const T*
                        ih[2], p->bin_start, sorted, sidx, p->qmax, g);
     return 1;
   }
-  // chunk size: a multiple of DPLR_SORT_CHUNK_ALIGN, at most max_chunks chunks,
-  // and few of them where that saves the column scan
-  constexpr int64_t ca = DPLR_SORT_CHUNK_ALIGN, few = 1024;
-  const int64_t chunk = n <= few * kPlaceScanChunks && g.nbins <= kPlaceScanBins
-                            ? few
-                            : std::max<int64_t>(ca, ((n + p->max_chunks - 1) / p->max_chunks + ca - 1) / ca * ca);
+  const int64_t chunk = sort_chunk(n, g.nbins, p->max_chunks, DPLR_SORT_CHUNK_ALIGN);
   const int nblk = (int)((n + chunk - 1) / chunk);
   {
     ProfScope ps(p, stage[0]);

@@ -27,6 +27,7 @@
 #pragma once
 
 #include "device_common.hpp"
+#include "launch_rules.hpp"
 
 namespace dplr {
 
@@ -336,12 +337,6 @@ __device__ __forceinline__ int block_exclusive_scan(const int* v, int* out, int 
   }
   return wsum[16];
 }
-
-// At most this many chunks: the placement adds up the chunk histograms itself,
-// all of a bin's in flight together, instead of k_bin_colscan (a launch of
-// 3.4 us at 16,384 particles).
-constexpr int kPlaceScanChunks = 16;
-constexpr int kPlaceScanBins = 4096;  // and at most this many bins (4 a thread)
 
 // Placement.  Every block first turns the bin totals into bin starts (an
 // exclusive scan in LDS; block 0 also publishes them as bin_start), then
