@@ -164,6 +164,7 @@ struct dplr_lr_plan_s {
   bool plane = false;         // whole z planes fit in LDS: spread + x and y transforms in one kernel
   bool ixy = false;           // inverse y and x transforms of a plane component in one kernel
   int last_split = 1;         // particle splits of the last compute
+  double last_k[3] = {0.0, 0.0, 0.0};  // 2 pi / L of its box
   int nzout = 3;              // spectra out of the z pass: three components, A and B, or the potential
   bool mixed = false;         // mesh outside the tuned kernels: mixed-radix path
   long long* mmesh = nullptr; // mixed-radix path: fixed-point mesh [Kz][Ky][Kx]
@@ -587,7 +588,7 @@ dplr_lr_status launch_step(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, c
     }
   }
   PoissonConsts pc;
-  for (int a = 0; a < 3; ++a) pc.two_pi_over_L[a] = 2.0 * M_PI / p->box[a];
+  for (int a = 0; a < 3; ++a) pc.two_pi_over_L[a] = p->last_k[a] = 2.0 * M_PI / p->box[a];
   pc.inv_4beta2 = 1.0 / (4.0 * p->cfg.beta * p->cfg.beta);
   // field components: three (ik) or the potential alone (analytic differentiation)
   const bool ad = (p->cfg.flags & DPLR_LR_DIFF_AD) != 0;
@@ -1269,9 +1270,7 @@ dplr_lr_status dplr_lr_debug_copy(dplr_lr_plan p, int32_t which, void* dst, int6
     // the passes keep A and B, not the three products
     const size_t cs = 2 * p->tsize;
     const unsigned nb = (unsigned)(((size_t)bytes + 256 * cs - 1) / (256 * cs));
-    double sc[3] = {0.0, 0.0, 0.0};
-    if (p->has_box)
-      for (int a = 0; a < 3; ++a) sc[a] = 2.0 * M_PI / p->box[a];
+    const double* sc = p->last_k;  // not the present box's, which set_box may have changed since
     if (nb > 0) {
       if (p->fp64)
         hipLaunchKernelGGL(k_field_spectra<double>, dim3(nb), dim3(256), 0, p->stream, (unsigned char*)dst,
@@ -1284,8 +1283,9 @@ dplr_lr_status dplr_lr_debug_copy(dplr_lr_plan p, int32_t which, void* dst, int6
     if (e != hipSuccess) return hip_fail(p, e, "debug copy");
     return DPLR_LR_OK;
   }
-  if (which == DPLR_LR_BUF_SPECTRUM && p->plane && p->last_split > 1) {
-    // the plane spread leaves one partial spectrum per particle split: report their sum
+  if (which == DPLR_LR_BUF_SPECTRUM && p->plane && p->geo.nsplit > 1) {
+    // the plane spread leaves one partial spectrum per particle split (of which the
+    // last compute took last_split): report their sum
     const size_t cs = 2 * p->tsize;
     if ((size_t)bytes % cs) return fail(p, DPLR_LR_E_INVALID, "size must be a whole number of complex values");
     const size_t n = (size_t)bytes / cs, nspec = (size_t)size / cs;
