@@ -716,8 +716,7 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
   // fused plane kernels (not for the int32 transforms, which run per axis)
   const bool fused = p->mfused > 0 && !q32;
   const int S = n >= kMixedSplitMinParticles ? p->msplit : 1;
-  // threads of a plane: at least 256, which the spread's particles keep busy
-  const int plane_thr = fused_threads((size_t)g.K[0] * g.K[1], 256, FusedPlane<T>::kThreads);
+  const int64_t nxy = (int64_t)g.K[0] * g.K[1];
   const int npart = fused ? p->mzblk : p->mblk;  // energy/virial block partials of this call
   if (p->lds_mplane) {
     // counting sort by (particle split, stencil-start plane) with the plane
@@ -731,7 +730,8 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
     const int nqpart = launch_sort<T, P>(p, gs, (const T*)ion_pos, (const T*)ion_q, (const T*)wc_pos, (const T*)wc_q,
                                          n_ion, n, ih, (T4<T>*)p->mrec, p->mspk, stage);
     if (fused)
-      hipLaunchKernelGGL((k_mixed_spread_xy<T, P>), dim3(g.K[2], S), dim3(plane_thr), p->mfused, s,
+      hipLaunchKernelGGL((k_mixed_spread_xy<T, P>), dim3(g.K[2], S),
+                         dim3(fused_spread_threads(nxy, FusedPlane<T>::kThreads)), p->mfused, s,
                          (const T4<T>*)p->mrec, (const int2*)p->mspk, (const int*)p->bin_start, gs,
                          (const unsigned*)p->qmax, nqpart, reinterpret_cast<cpx<T>*>(p->mmesh));
     else
@@ -768,7 +768,7 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
     if (fused) {
       const int C = p->mzc;
       hipLaunchKernelGGL(k_mixed_fftz_poisson<T>, dim3((unsigned)p->mzblk),
-                         dim3(fused_threads(2 * (size_t)C * g.K[2], 64, kFusedZThreads)),
+                         dim3(fused_z_threads((int64_t)C * g.K[2], p->mzblk, kFusedZThreads)),
                          (size_t)(2 * C + 1) * g.K[2] * sizeof(cpx<T>), s, (const cpx<T>*)p->mmesh, S, field,
                          field + ntot, p->G, g.K[0], g.K[1], g.K[2], C, pc, 1.0, p->partials);
     } else {
@@ -784,7 +784,8 @@ dplr_lr_status launch_mixed(dplr_lr_plan p, int64_t n_ion, const void* ion_pos, 
     {
       ProfScope ps(p, 14);
       if (fused)
-        hipLaunchKernelGGL(k_mixed_ifft_xy<T>, dim3(g.K[2], 2), dim3(plane_thr), p->mfused, s, (const cpx<T>*)field,
+        hipLaunchKernelGGL(k_mixed_ifft_xy<T>, dim3(g.K[2], 2),
+                           dim3(fused_inverse_threads(nxy, FusedPlane<T>::kThreads)), p->mfused, s, (const cpx<T>*)field,
                            (const cpx<T>*)(field + ntot), g.K[0], g.K[1], (T*)p->mpacked);
       else if (q32) launch_mixed_dft_q32<T>(p, field, 3, +1, (T*)p->mpacked);
       else launch_mixed_fft<T>(p, field, 3, +1, (T*)p->mpacked);

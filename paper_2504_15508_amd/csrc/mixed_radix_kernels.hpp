@@ -459,15 +459,6 @@ constexpr int kFusedZMaxPts = 2048;  // C Kz bound of k_mixed_fftz_poisson (one 
 constexpr int kFusedZThreads = 256;  // its most threads
 constexpr int kFusedZPer = kFusedZMaxPts / kFusedZThreads;  // points per thread, one field
 
-// Threads of a block of the fused kernels for pts points: one radix-10
-// butterfly each, a multiple of 64 in [least, most].  More threads only wait
-// at the barriers (12 x 18 planes in FP64: inverse pass 6.6 us with 256
-// threads, 8.7 with 1,024; the z pass of 120^3 with 256 and 512 threads
-// holds 5 blocks a compute unit either way).
-inline int fused_threads(size_t pts, int least, int most) {
-  return std::max(least, (int)std::min<size_t>((pts / 10 + 63) / 64 * 64, (size_t)most));
-}
-
 // floor(x / d) for 0 <= x, d < 2^23 from the float reciprocal inv = 1 / d:
 // the estimate is off by at most one either way and is corrected.
 __device__ __forceinline__ int qdiv(int x, int d, float inv) {
