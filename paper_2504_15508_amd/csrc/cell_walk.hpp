@@ -47,9 +47,11 @@ struct CellWalk {
     }
     if (!on) b = a;
   }
-  constexpr void begin(int dq) {
-    segment(0, j0, j1);
-    segment(dq, j0n, j1n);
+  // chunk number `chunk` of segment q (one or two steps, dq, between segments)
+  constexpr void begin(int q, int chunk, int dq) {
+    segment(q, j0, j1);
+    j0 = j1 - j0 > kScanChunk * chunk ? j0 + kScanChunk * chunk : j1;
+    segment_ahead(q + dq);
   }
   // candidates of the present chunk (0 .. kScanChunk)
   constexpr int left() const { return j1 - j0 < kScanChunk ? j1 - j0 : kScanChunk; }
@@ -60,8 +62,9 @@ struct CellWalk {
   constexpr void next_segment(int q) {
     j0 = j0n;
     j1 = j1n;
-    segment(q < kSegments ? q : kSegments - 1, j0n, j1n);
+    segment_ahead(q);
   }
+  constexpr void segment_ahead(int q) { segment(q < kSegments ? q : kSegments - 1, j0n, j1n); }
 };
 
 }  // namespace mlp

@@ -361,8 +361,12 @@ __global__ void __launch_bounds__(128) k_norm_finish(double* __restrict__ acc, f
 // ---------------------------------------------------------------------------
 constexpr int kDescThreads = 64;
 constexpr int kDescParts = kDescThreads / kDescLanes;
-constexpr int kNbrMax = 64;
-static_assert(kScanChunk <= 32 && kNbrMax % kDescLanes == 0, "one word of candidate bits per chunk");
+// A list takes another chunk while it holds at most kNbrMax neighbours: 78 entries
+// and a spare one, the most with which eight blocks of k_correction fit the LDS
+// of a compute unit.  (Water has 36 neighbours on average.)
+constexpr int kNbrMax = 62;
+constexpr int kNbrList = kNbrMax + kScanChunk + 1;
+static_assert(kScanChunk <= 32, "one word of candidate bits per chunk");
 
 // Pairs per round of the accumulation: every lane of a particle forms one
 // pair's quantities (once per pair), and then every lane runs its eight orders
@@ -486,12 +490,13 @@ __device__ __forceinline__ void descriptor_row(float (&T)[4], const f32x4& acc, 
   T[0] = T0;
 }
 
-// Lists the neighbours number base .. base + kNbrMax - 1 of particle i (at pi; on:
-// there is one; this is lane g of its four) and returns how many there are in
-// all.  The whole wave calls it.
-__device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, int g,
-                                               const float4* __restrict__ cpos, const int* __restrict__ start,
-                                               const CellGeo& c, int base, int* list) {
+// Lists the next neighbours of the particle at pi (on: there is one; this is lane
+// g of its four), from chunk `chunk` of segment q on, until its candidates end
+// (q = kSegments) or a list of the wave is full, and returns how many.  The whole
+// wave calls it.
+__device__ __forceinline__ int scan_neighbours(const float4 pi, bool on, int g, const float4* __restrict__ cpos,
+                                               const int* __restrict__ start, const CellGeo& c, int& q, int& chunk,
+                                               int* list) {
   const float rc2 = c.rc * c.rc;
   CellWalk w{start, c.nc[0], c.nc[1], c.nc[2], min((int)(pi.x * c.cinv[0]), c.nc[0] - 1),
              min((int)(pi.y * c.cinv[1]), c.nc[1] - 1), min((int)(pi.z * c.cinv[2]), c.nc[2] - 1), on, 0, 0, 0, 0};
@@ -503,10 +508,10 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
     sz = z < 0 ? c.L[2] : z >= w.nz ? -c.L[2] : 0.0f;
   };
   const int dq = __any(w.at_end()) ? 1 : 2;  // second ranges only where a particle of the wave has one
-  int cnt = 0, q = 0;
+  int cnt = 0;
   float sx, sy, sz;
-  w.begin(dq);
-  shifts(0, sx, sy, sz);
+  w.begin(q, chunk, dq);
+  shifts(q, sx, sy, sz);
   // candidates j0 + 4 u + g, u < kScan, of the next chunk (those past the range are
   // masked below; the array has kScanPad spare entries for the last range's)
   float3 pj[kScan];
@@ -516,7 +521,7 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
     for (int u = 0; u < kScan; ++u) pj[u] = *reinterpret_cast<const float3*>(src + kDescLanes * u);
   };
   fetch();
-  while (q < kSegments) {
+  while (q < kSegments && !__any(cnt > kNbrMax)) {
     const int jc = w.j0 + g;
     const int left = w.left();
     // bit 4 u + g of the particle's word: candidate 4 u + g is inside the cutoff
@@ -535,8 +540,10 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
     }
     // the next chunk's candidates arrive while this one's are listed
     w.advance();
+    ++chunk;
     if (!__any(w.j0 < w.j1)) {
       q += dq;
+      chunk = 0;
       w.next_segment(q + dq);
       shifts(min(q, kSegments - 1), sx, sy, sz);
     }
@@ -547,12 +554,11 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
     word &= (1u << left) - 1u;  // what lies past the range is dropped
     // each lane lists its own candidates at their places in candidate order
     // (the others go to a spare entry)
-    int place = cnt - base + __popc(word & ((1u << g) - 1u));
+    int place = cnt + __popc(word & ((1u << g) - 1u));
     const unsigned own = word >> g;
 #pragma unroll
     for (int u = 0; u < kScan; ++u) {
-      const unsigned at = own & (1u << (kDescLanes * u)) ? (unsigned)place : (unsigned)kNbrMax;
-      list[min(at, (unsigned)kNbrMax)] = jc + kDescLanes * u;
+      list[own & (1u << (kDescLanes * u)) ? place : kNbrList - 1] = jc + kDescLanes * u;
       place += __popc(own & (0xfu << (kDescLanes * u)));
     }
     cnt += __popc(word);
@@ -562,23 +568,26 @@ __device__ __forceinline__ int scan_neighbours(const float4 pi, int i, bool on, 
 
 // The descriptor of particle i into acc and T0 of its four lanes (of which this
 // is lane g); list and S: the particle's LDS.  Returns the neighbour count.
-// The whole wave calls it.  More than kNbrMax neighbours are taken in rounds;
+// The whole wave calls it.  More neighbours than a list holds are taken in rounds, each
+// of which goes on where the one before stopped (a scan of all candidates in every
+// round took 16.7 ms for 20,000 particles in a droplet of 4 A; this way 2.3);
 // the sums wait in the particle's row of T meanwhile, so that they are not live
 // during a scan (they would cost it a third of its registers).
 __device__ __forceinline__ int describe(f32x4 (&acc)[8], float (&T0)[8], const float4 pi, int i, bool on, int g,
                                         const float4* __restrict__ cpos, const int* __restrict__ start,
                                         const CellGeo& c, float* __restrict__ Tbuf, int* list, PairSlots& S) {
   float4* rows = reinterpret_cast<float4*>(Tbuf + (size_t)i * 128);
-  int total = 0;
-  for (int base = 0;; base += kNbrMax) {
-    total = scan_neighbours(pi, i, on, g, cpos, start, c, base, list);
+  int total = 0, q = 0, chunk = 0;
+  do {
+    const bool first = q + chunk == 0;
+    const int cnt = scan_neighbours(pi, on, g, cpos, start, c, q, chunk, list);
     wave_lds_fence();
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       acc[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       T0[m] = 0.0f;
     }
-    if (base > 0) {
+    if (!first) {
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         const float4 r = on ? rows[g + 4 * m] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -588,15 +597,17 @@ __device__ __forceinline__ int describe(f32x4 (&acc)[8], float (&T0)[8], const f
         acc[m] = f32x4{T[0], T[1], T[2], T[3]};
       }
     }
-    accumulate_pairs(acc, T0, pi, cpos, list, min(max(total - base, 0), kNbrMax), g, c, S);
-    if (!__any(total > base + kNbrMax)) break;
+    accumulate_pairs(acc, T0, pi, cpos, list, cnt, g, c, S);
+    total += cnt;
+    if (q < kSegments) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      float T[4];
-      descriptor_row(T, acc[m], T0[m], g);
-      if (on) rows[g + 4 * m] = make_float4(T[0], T[1], T[2], T[3]);
+      for (int m = 0; m < 8; ++m) {
+        float T[4];
+        descriptor_row(T, acc[m], T0[m], g);
+        if (on) rows[g + 4 * m] = make_float4(T[0], T[1], T[2], T[3]);
+      }
     }
-  }
+  } while (q < kSegments);
   return total;
 }
 
@@ -639,7 +650,7 @@ __global__ void __launch_bounds__(kDescThreads, 4) k_descriptor(const float4* __
                                                                 const float* __restrict__ params,
                                                                 float* __restrict__ Tout,
                                                                 unsigned short* __restrict__ X, CellGeo c) {
-  __shared__ int lists[kDescParts][kNbrMax + 1];
+  __shared__ int lists[kDescParts][kNbrList];
   __shared__ __align__(16) PairSlots slots[kDescParts];
   const int g = threadIdx.x & (kDescLanes - 1), p = threadIdx.x / kDescLanes;
   const int i = blockIdx.x * kDescParts + p;
@@ -741,7 +752,7 @@ constexpr int kFragOfs[4] = {0, 16, 24, 32};  // 36 fragments of 64 lanes x 8 va
 
 union CorrLds {
   struct {
-    int lists[kCorrRows][kNbrMax + 1];
+    int lists[kCorrRows][kNbrList];
     PairSlots slots[kCorrRows];
   } d;
   struct {

@@ -1,5 +1,5 @@
 """The index walk of the neighbour scan on the CPU: every candidate of the 27
-cells once, and no entry read behind the sorted particles' spare ones, where the
+cells once, also where the walk stops and goes on, and no entry read behind the sorted particles' spare ones, where the
 16 particles of a wave have ranges of very different lengths.  (The scan drops
 what lies past a particle's range, so results cannot show such a read.)"""
 import ctypes
@@ -32,7 +32,7 @@ extern "C" int walk(int n, const int* nc, const int* start, const int* cell, lon
       ends = ends || w[p].at_end();
     }
     const int dq = ends ? 1 : 2;
-    int q = 0;
+    int q = 0, chunk = 0;
     auto read = [&]() {  // lanes g < kDescLanes, loads u < kScan: j0 + g + kDescLanes u
       for (int p = 0; p < 16; ++p) {
         const int last = w[p].j0 + (kDescLanes - 1) + kDescLanes * (kScan - 1);
@@ -41,7 +41,7 @@ extern "C" int walk(int n, const int* nc, const int* start, const int* cell, lon
       }
       return true;
     };
-    for (int p = 0; p < 16; ++p) w[p].begin(dq);
+    for (int p = 0; p < 16; ++p) w[p].begin(0, 0, dq);
     if (!read()) return -1;
     while (q < kSegments) {
       bool more = false;
@@ -51,11 +51,19 @@ extern "C" int walk(int n, const int* nc, const int* start, const int* cell, lon
         w[p].advance();
         more = more || w[p].j0 < w[p].j1;
       }
+      ++chunk;
       if (!more) {
         q += dq;
+        chunk = 0;
         for (int p = 0; p < 16; ++p) w[p].next_segment(q + dq);
       }
       if (!read()) return -1;
+      // a scan that stopped here goes on from the same place
+      for (int p = 0; p < 16 && q < kSegments; ++p) {
+        CellWalk r = w[p];
+        r.begin(q, chunk, dq);
+        if (r.j0 != w[p].j0 || r.j1 != w[p].j1 || r.j0n != w[p].j0n || r.j1n != w[p].j1n) return -3;
+      }
     }
   }
   return most;
