@@ -22,8 +22,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 # A step of a few hundred particles takes the GPU 40 us, so the calls around it
 # count: the device is switched only when another one is current, and the
-# stream handle is read without building a Stream object.
+# stream handle is read without building a Stream object (where PyTorch has the
+# function for that; it is not a public one).
 _current = contextlib.nullcontext()
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _on(device: torch.device):
@@ -31,7 +33,9 @@ def _on(device: torch.device):
 
 
 def _stream(device: torch.device) -> int:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(torch.cuda.current_device() if device.index is None else device.index)
 
 
 class Plan:
