@@ -119,9 +119,12 @@ __global__ void __launch_bounds__(256) k_cell_count(const float* __restrict__ io
 
 // Exclusive scan of the cell counts by several blocks: block b adds up the
 // counts before its tile by itself (reads that stream from L2), then scans the
-// tile; the last one also writes start[ncells].  Its work grows with the square
-// of the cell count, so larger grids keep the one-block scan (k_bin_scan).
-constexpr int kScanTile = 2048, kScanCells = 1 << 17;
+// tile; the last one also writes start[ncells].  Its reads grow with the square
+// of the cell count, those of one block with a carried sum (k_bin_scan) do not:
+// 6.2 and 27 us at 32,768 cells, 14.5 and 113 at 140,608, 77 and 779 at 10^6, 2,890
+// and 6,470 at 8.4 x 10^6, where the line lies: twice as many cells would be four
+// times the one and twice the other.
+constexpr int kScanTile = 2048, kScanCells = 1 << 23;
 __global__ void __launch_bounds__(1024) k_cell_scan(const int* __restrict__ count, int* __restrict__ start,
                                                     int ncells) {
   __shared__ int red[16];
