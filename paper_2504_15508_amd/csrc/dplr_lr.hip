@@ -284,8 +284,8 @@ bool choose_geometry(dplr_lr_plan p) {
   const int ept = p->fp64 ? fft_ept<double>() : fft_ept<float>();
 
   // plane spread: one z plane of 64-bit accumulators (rows of Kx + p - 1),
-  // reused for the x- and y-transform tiles, 1024 threads holding at most 16
-  // values each
+  // reused for the x- and y-transform tiles; each call picks its threads
+  // (256, 512 or 1024) with at most 16 mesh points each
   {
     const size_t b_acc = (size_t)Ky * (Kx + P - 1) * sizeof(long long);
     const size_t b_tx = (size_t)(Ky / 2) * (padded_len(Kx) + 1) * cs;
@@ -294,7 +294,6 @@ bool choose_geometry(dplr_lr_plan p) {
     p->plane = b <= budget && (long)Kx * Ky <= 16L * 1024 && (long)g.Kh * Ky <= 16L * 1024;
     if (p->plane) {
       p->lds_spread = b;
-      p->thr_spread = 1024;
       const int per_cu = std::max<int>(1, (int)(p->lds_budget / (b + 1024)));
       const int target = std::min(1024, 256 * per_cu);
       g.nsplit = 1;

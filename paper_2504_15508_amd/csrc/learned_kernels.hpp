@@ -737,9 +737,9 @@ constexpr int kLW1t = 0, kLW2t = kLW1t + kH * kPadIn, kLW3t = kLW2t + kH * kPadH
 // force head, with nothing but the forces written.  (As two kernels the
 // descriptor and the network input, 768 bytes a particle, went through memory:
 // at 288,768 particles the descriptor kernel spent 85 of its 218 us writing them
-// and the network kernel 89 us mostly reading them; this kernel takes 219.)
-// What is left is VALU issue: about 83 us of scan, 88 of pairs, 22 of network, the
-// rest the inputs and the head.
+// and the network kernel 89 us mostly reading them; this kernel takes 213.)
+// What is left is VALU issue: of 222 us, when full lists began their scan anew,
+// about 83 were scan, 88 pairs and 22 network, the rest the inputs and the head.
 // Two waves hold 16 particles each for the descriptor; for the network, wave w
 // computes features 32 w .. 32 w + 31 of all 32 particles: weights as the A
 // operand in fragment order straight from L2 (36 KB, read by every block; LDS

@@ -642,8 +642,8 @@ __device__ __forceinline__ void stage_inplace(cpx<T>* buf, int N, int nrows, int
 }
 
 // In-place unnormalised DFT of every row, X[k] = sum_n x[n] exp(-+2 pi i n k
-// / N) (INV: +), stages of radix 4, 2, 3, 5 in that order of preference; tw
-// holds the N roots of unity of that sign.  nrows N <= PER blockDim.x, so no
+// / N) (INV: +), stages of the radices that pick_radix chooses; tw holds the N
+// roots of unity of that sign.  nrows N <= PER blockDim.x, so no
 // thread has more than ceil(PER / R) butterflies in a stage.
 #ifndef DPLR_MIXED_MAX_RADIX
 #define DPLR_MIXED_MAX_RADIX 12

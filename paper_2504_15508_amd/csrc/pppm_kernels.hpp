@@ -382,8 +382,7 @@ __global__ void __launch_bounds__(1024) k_bin_place(const T* __restrict__ ion_po
   if (staged) {
     // many totals go to LDS first, coalesced: a thread's stretch of them read
     // straight from memory is one line per load (16,384 bins of a 256^3 mesh:
-    // placement 78 us, this way 69, with one store for start and index
-    // below 58; with 1,920 bins no gain)
+    // placement 78 us, this way 69; with 1,920 bins no gain)
     copy_g2s<8>(start, total, g.nbins);
     __syncthreads();
   }
@@ -1020,8 +1019,9 @@ __global__ void k_sum_partials(cpx<T>* __restrict__ dst, const cpx<T>* __restric
 }
 
 // Final FP64 reduction of the z-pass partials with a fixed tree (bitwise
-// deterministic); run by block 0 of the inverse y pass, which follows the
-// z pass on the stream.
+// deterministic), by one block of a pass that follows the z pass on the
+// stream: block 0 of the inverse y pass (k_ffty), or a block of its own of the
+// inverse plane pass (k_ifft_xy).
 __device__ void reduce_partials(const double* __restrict__ partials, int nblk, double pre,
                                 double* __restrict__ energy, double* __restrict__ virial, double* red) {
   // red: 7 * blockDim.x doubles of LDS
@@ -1129,8 +1129,8 @@ __global__ void __launch_bounds__(kFftyThreads) k_ffty(cpx<T>* __restrict__ data
 //   z): two transforms and two spectra written instead of three (nout = 3).  The
 //   integer n' are exact in FP32; the passes that read A multiply by n'_x and
 //   n'_y.  nout = 2 pays where the transforms or the spectra are large: FP64 at
-//   128^3 (42.6 -> 29.3 us with the register change above) and FP32 at 256^3
-//   (124 -> 74 us, of which 3 -> 2 spectra is the larger part).  FP32 planes
+//   128^3 (42.6 -> 31 us, with 8 values a thread instead of 16) and FP32 at 256^3
+//   (124 -> 78 us, of which 3 -> 2 spectra is the larger part).  FP32 planes
 //   that fit in LDS keep three: at 128^3 the 1.6 us it saves here are lost to the
 //   factors in k_ifft_xy.  nout = 1: the potential spectrum G Q^.
 //   e  = sum w G |Q^|^2,  w = 1 on the kx = 0 and kx = Kx/2 planes, else 2;
@@ -1744,8 +1744,6 @@ template <typename T>
 struct __attribute__((aligned(16))) Chunk16 {
   T v[16 / sizeof(T)];
 };
-
-
 
 template <typename T, int P>
 __global__ void __launch_bounds__(256) k_gather_ad(const T* __restrict__ phi, const T4<T>* __restrict__ sorted,
